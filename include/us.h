@@ -46,8 +46,9 @@ typedef enum {
 #define US_WORDS_PER_LT 4   /* 8 x 32 union-mask bits = four 64-bit words  */
 #define US_PAYLOAD_PAD 16   /* zero bytes after the payload                */
 #define US_N_MAX 32         /* widest activation matrix of one kernel pass */
-#define US_N_LIMIT 1024     /* widest activation matrix; N > US_N_MAX runs as
-                               slabs of US_N_MAX columns, each streaming W */
+#define US_N_LIMIT 1024     /* widest activation matrix; with a forced
+                               configuration N > US_N_MAX runs as slabs of
+                               US_N_MAX columns, each streaming W */
 #define US_K_MAX 130048     /* K bound: int32 headroom of the kernel's scaled sums */
 
 /*
@@ -260,7 +261,11 @@ typedef struct {
  * min(N, US_N_MAX) columns, for a matrix of `bits`-bit values (4 or 2) that
  * is row-reordered when `reordered` != 0 (its stages are larger). The
  * paper claims a shape-aware kernel selection (Section I, contributions)
- * without describing it; this is ours. Host only; for tuning and reporting.
+ * without describing it; this is ours. It covers the configurations that
+ * options can force; automatic us_spmm calls above 16 columns take a kernel
+ * family of their own (one launch for all columns), chosen by its own cost
+ * model, which these fields do not describe. Host only; for tuning and
+ * reporting.
  * Same argument errors as us_spmm; US_ERR_ARG if no configuration fits.
  */
 us_status us_spmm_plan(int32_t M, int32_t K, int32_t N, int32_t bits, int32_t reordered, const us_spmm_opts *opts,
@@ -289,10 +294,11 @@ us_status us_spmm_workspace_size(int32_t M, int32_t K, int32_t N, const us_spmm_
  *            w->bits = 2 multiplies a W2A4 matrix
  *   x      : device, N x K row-major INT4, two values per byte along K
  *            (even k in the low nibble), 16-byte aligned
- *   N      : 1..US_N_LIMIT activation columns; beyond US_N_MAX (32) the
- *            call runs one pass per slab of 32 columns (the last one
- *            narrower), each with its own configuration and each reading W
- *            again: prefill-sized N at decode-kernel cost per slab
+ *   N      : 1..US_N_LIMIT activation columns. Automatic calls above 16
+ *            columns run as one launch of the tile kernel; with a forced
+ *            configuration, beyond US_N_MAX (32), as one pass per slab of 32
+ *            columns (the last one narrower), each with its own
+ *            configuration and each reading W again
  *   y      : device int32, N x M row-major (y[n * M + m] = Y[m][n])
  *   scale  : device float32[M] or NULL; with it, y_f32[n * M + m] =
  *            fl32(fl32(Y[m][n]) * scale[m]) is written too (the dequant
