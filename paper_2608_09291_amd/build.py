@@ -36,10 +36,10 @@ HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-fno-stric
 # default, with which they fit the registers of four wavefronts per SIMD,
 # and so do the row-reordered ones up to 16 columns (us_spmm_perm.hip),
 # which measured 1 % slower with it.
-# The tile kernels (us_spmm_tile_*.hip) keep it too: the other strategy does
-# not compile them.
+# The tile kernels (us_spmm_tile_*.hip) keep it too, as the other strategy does
+# not compile them, and so does the dense GEMM, which was measured with it.
 DEFAULT_SCHED_UNITS = ("us_spmm_wide8.hip", "us_spmm_perm.hip", "us_spmm_tile_plain.hip", "us_spmm_tile_perm.hip",
-                       "us_spmm_tile_w2.hip")
+                       "us_spmm_tile_w2.hip", "us_gemm.hip")
 
 
 def hip_flags(source: str) -> list:

@@ -9,6 +9,7 @@
 #include <atomic>
 
 #include "us.h"
+#include "us_device.h"
 #include "us_spmm_burst.h"
 #include "us_spmm_kernel.h"
 #include "us_spmm_tile.h"
@@ -150,19 +151,6 @@ void choose_config(int M, int K, int N, bool perm, int bits, int n_cu, int wpg_o
     }
 }
 
-// Compute units of the current device (queried once per device).
-int device_cus() {
-    static std::atomic<int> cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int n = cached[dev].load(std::memory_order_relaxed);
-    if (n <= 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cached[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
-
 // The launch of one slab of up to US_N_MAX columns: a chunked configuration
 // (us_spmm_kernel.h) or a single-pass one (us_spmm_burst.h).
 struct Plan {
@@ -240,7 +228,7 @@ extern "C" us_status us_spmm_plan(int32_t M, int32_t K, int32_t N, int32_t bits,
     if (st != US_OK) return st;
     if ((st = check_opts(opts)) != US_OK) return st;
     Plan pl;
-    st = make_plan(M, K, std::min(N, US_N_MAX), reordered != 0, bits, opts, device_cus(), true, pl);
+    st = make_plan(M, K, std::min(N, US_N_MAX), reordered != 0, bits, opts, us_device::compute_units(), true, pl);
     if (st != US_OK) return st;
     if (pl.burst) {
         *split_k = pl.b.wpg;
@@ -288,7 +276,7 @@ extern "C" us_status us_spmm(const us_iebme_dev *w, const uint8_t *x, int32_t N,
     if (bits == 2 && perm) return US_ERR_ARG;              // no reordered 2-bit kernels
     if ((st = check_opts(opts)) != US_OK) return st;
 
-    const int n_cu = device_cus();
+    const int n_cu = us_device::compute_units();
     SpmmArgs a;
     a.bm32 = (const uint32_t *)w->bitmaps;
     a.off = w->offsets;

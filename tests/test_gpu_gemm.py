@@ -1,0 +1,48 @@
+"""GPU parity of every built configuration of the dense INT8 GEMM.
+
+The shapes are chosen so that the automatic choice takes the configuration
+named beside them on a 256-CU GPU, with rows, columns and k that do not fill
+its tiles, chunks or slices. Results are exact.
+"""
+import numpy as np
+import pytest
+
+from oracle import product
+from paper_2608_09291_amd import binding
+from test_gpu_spmm import announce, torch_cuda  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    (48, 64, 4),          # 1 x 1 blocks, 1 x 1 wavefronts, 1 slices
+    (16, 576, 4),         # 1 x 1 blocks, 1 x 1 wavefronts, 8 slices
+    (16, 320, 21),        # 1 x 1 blocks, 1 x 1 wavefronts, 4 slices
+    (4528, 320, 1),       # 2 x 1 blocks, 1 x 1 wavefronts, 4 slices
+    (5584, 2752, 1),      # 2 x 1 blocks, 1 x 1 wavefronts, 8 slices
+    (4112, 320, 17),      # 2 x 2 blocks, 1 x 1 wavefronts, 4 slices
+    (4208, 576, 18),      # 2 x 2 blocks, 1 x 1 wavefronts, 8 slices
+    (8880, 832, 17),      # 4 x 2 blocks, 1 x 1 wavefronts, 4 slices
+    (9808, 1600, 17),     # 4 x 2 blocks, 1 x 1 wavefronts, 8 slices
+    (10032, 448, 132),    # 4 x 4 blocks, 1 x 1 wavefronts, 4 slices
+    (7024, 704, 100),     # 4 x 4 blocks, 1 x 1 wavefronts, 8 slices
+    (10704, 64, 98),      # 2 x 4 blocks, 2 x 2 wavefronts, 1 slices
+    (8464, 64, 652),      # 4 x 4 blocks, 2 x 2 wavefronts, 1 slices
+    (8208, 704, 200),     # 2 x 4 blocks, 2 x 2 wavefronts, several chunks
+    (12304, 704, 500),    # 4 x 4 blocks, 2 x 2 wavefronts, several chunks
+    (48, 130048, 3),      # the longest k
+]
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES)
+def test_every_configuration(torch_cuda, M, K, N):
+    torch = torch_cuda
+    announce(f"gemm M={M} K={K} N={N}")
+    rng = np.random.default_rng(M + K + N)
+    W = rng.integers(-128, 128, size=(M, K), dtype=np.int8)
+    Xt = rng.integers(-128, 128, size=(N, K), dtype=np.int8)
+    y = torch.full((N + 1, M), -7, dtype=torch.int32, device="cuda")
+    binding.gemm_i8(torch.from_numpy(W).cuda(), torch.from_numpy(Xt).cuda(), M, K, N, y)
+    torch.cuda.synchronize()
+    out = y.cpu().numpy()
+    assert np.array_equal(out[:N].T, product.to_int32(product.matmul_c(W, Xt)))
+    assert (out[N] == -7).all()                       # nothing past the last column

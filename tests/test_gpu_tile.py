@@ -30,7 +30,7 @@ SHAPES = [
     (6416, 576, 100),       # 2 x 4, 1, 4
     (4112, 8320, 50),       # 2 x 4, 1, 8
     (12304, 1984, 250),     # 4 x 4, 2, 2
-    (12304, 64, 200),       # 2 x 8, 4, 1
+    (12304, 704, 200),      # 2 x 8, 4, 1
     (4112, 64, 1021),       # 3 x 8, 4, 1
 ]
 

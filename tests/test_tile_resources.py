@@ -1,4 +1,4 @@
-"""Register budget and M0 use of the built tile kernels (host only: compiles to gfx950 assembly)."""
+"""Register budget and M0 use of the built tile and dense GEMM kernels (host only: compiles to gfx950 assembly)."""
 import concurrent.futures as cf
 import os
 import re
@@ -9,7 +9,7 @@ import pytest
 from paper_2608_09291_amd import build
 
 CSRC = build.CSRC
-UNITS = ("us_spmm_tile_plain", "us_spmm_tile_perm", "us_spmm_tile_w2")
+UNITS = ("us_spmm_tile_plain", "us_spmm_tile_perm", "us_spmm_tile_w2", "us_gemm")
 
 
 @pytest.fixture(scope="module")
@@ -26,7 +26,7 @@ def texts(tmp_path_factory):
         assert r.returncode == 0, r.stderr[-2000:]
         return open(out).read()
 
-    with cf.ThreadPoolExecutor(max_workers=3) as ex:
+    with cf.ThreadPoolExecutor(max_workers=4) as ex:
         return list(ex.map(compile_unit, UNITS))
 
 
@@ -35,16 +35,17 @@ def test_registers_fit_and_nothing_spills(texts):
     for text in texts:
         for m in re.finditer(r"\.amdhsa_kernel (\S+)(.*?)\.end_amdhsa_kernel", text, re.S):
             g = re.search(r"us_spmm_tile_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)", m.group(1))
-            if not g:
+            d = re.search(r"us_gemm_i8_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", m.group(1))
+            if not g and not d:
                 continue
-            lw, perm = int(g.group(6)), g.group(8) == "1"
-            lw = 7 if perm and lw == 8 else lw
+            lw = int(g.group(6) if g else d.group(7))
+            lw = 7 if g and g.group(8) == "1" and lw == 8 else lw
             vgpr = int(re.search(r"\.amdhsa_next_free_vgpr (\d+)", m.group(2)).group(1))
             scratch = int(re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", m.group(2)).group(1))
             assert vgpr <= (512 // lw) // 8 * 8, (m.group(1), vgpr, lw)
             assert scratch == 0, m.group(1)
             n += 1
-    assert n >= 3 * 14, n
+    assert n >= 3 * 14 + 13, n
 
 
 def test_m0_is_only_the_direct_loads(texts):
