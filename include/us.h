@@ -262,10 +262,10 @@ typedef struct {
  * is row-reordered when `reordered` != 0 (its stages are larger). The
  * paper claims a shape-aware kernel selection (Section I, contributions)
  * without describing it; this is ours. It covers the configurations that
- * options can force; automatic us_spmm calls above 16 columns take a kernel
- * family of their own (one launch for all columns), chosen by its own cost
- * model, which these fields do not describe. Host only; for tuning and
- * reporting.
+ * options can force, which automatic us_spmm calls use for some narrow
+ * shapes; the others take the tile kernel (one launch for all columns) in a
+ * configuration chosen by its own cost model, which these fields do not
+ * describe. Host only; for tuning and reporting.
  * Same argument errors as us_spmm; US_ERR_ARG if no configuration fits.
  */
 us_status us_spmm_plan(int32_t M, int32_t K, int32_t N, int32_t bits, int32_t reordered, const us_spmm_opts *opts,
@@ -294,10 +294,9 @@ us_status us_spmm_workspace_size(int32_t M, int32_t K, int32_t N, const us_spmm_
  *            w->bits = 2 multiplies a W2A4 matrix
  *   x      : device, N x K row-major INT4, two values per byte along K
  *            (even k in the low nibble), 16-byte aligned
- *   N      : 1..US_N_LIMIT activation columns. Automatic calls above 16
- *            columns run as one launch of the tile kernel; with a forced
- *            configuration, beyond US_N_MAX (32), as one pass per slab of 32
- *            columns (the last one narrower), each with its own
+ *   N      : 1..US_N_LIMIT activation columns, in one launch; with a
+ *            forced configuration, beyond US_N_MAX (32), one pass per slab
+ *            of 32 columns (the last one narrower), each with its own
  *            configuration and each reading W again
  *   y      : device int32, N x M row-major (y[n * M + m] = Y[m][n])
  *   scale  : device float32[M] or NULL; with it, y_f32[n * M + m] =

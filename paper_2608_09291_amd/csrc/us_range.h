@@ -41,14 +41,15 @@ __host__ __device__ inline uint32_t range_bytes(uint32_t oe, uint32_t a0, uint32
     return (uint32_t)(16u * nq < room ? 16u * nq : room);
 }
 
-// The same for offsets of whole LTs (multiples of four values), in 32-bit
-// arithmetic only: what ends before the first staged byte is one piece
-// instead of none (still inside the payload), everything else is equal.
+// The same for offsets of whole LTs (multiples of four values) in 32-bit
+// arithmetic and without the overhang: the 16-byte pieces that hold values
+// [first staged value, oe). A window that reaches past them reads whatever the
+// stage holds there and selects none of it.
 template <int BITS>
-__host__ __device__ inline uint32_t range_bytes32(uint32_t oe, uint32_t a0, uint32_t pay_bytes, uint32_t max_pieces) {
+__host__ __device__ inline uint32_t value_bytes(uint32_t oe, uint32_t a0, uint32_t pay_bytes, uint32_t max_pieces) {
     constexpr int kValShift = BITS == 4 ? 1 : 2;          // log2(values per byte)
     const uint32_t e = oe >> kValShift, room = pay_bytes - a0;
-    const uint32_t n = ((e > a0 ? e - a0 : 0u) + 23u) & ~15u;
+    const uint32_t n = ((e > a0 ? e - a0 : 0u) + 15u) & ~15u;
     const uint32_t most = n < 16u * max_pieces ? n : 16u * max_pieces;
     return most < room ? most : room;
 }

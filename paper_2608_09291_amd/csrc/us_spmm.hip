@@ -102,9 +102,9 @@ bool burst_from_opts(const us_spmm_opts &o, int nkb, int N, bool perm, int bits,
 // or ring payload staging only (0: either). perm: the LTs are row-reordered
 // (their stages hold two more per-LT arrays); bits: payload value width
 // (2-bit chunks stage half the payload bytes); ch_only > 0 fixes the chunk
-// length.
+// length. gens: generations of workgroups the choice runs in.
 void choose_config(int M, int K, int N, bool perm, int bits, int n_cu, int wpg_only, int staging, int ch_only,
-                   int &wpg, int &cfg) {
+                   int &wpg, int &cfg, long &gens_out) {
     const int nrb = M / 16, nkb = K / 64;
     long best[6] = {0, 0, 0, 0, 0, 0};
     wpg = 0;
@@ -146,6 +146,7 @@ void choose_config(int M, int K, int N, bool perm, int bits, int n_cu, int wpg_o
                 for (int k = 0; k < 6; ++k) best[k] = key[k];
                 wpg = w;
                 cfg = idx;
+                gens_out = gens;
             }
         }
     }
@@ -156,6 +157,7 @@ void choose_config(int M, int K, int N, bool perm, int bits, int n_cu, int wpg_o
 struct Plan {
     bool burst = false;
     int wpg = 0, cfg = -1;     // chunked: wavefronts per workgroup, kCfgs index
+    long gens = 0;             // and generations of workgroups
     BurstPlan b;               // burst
 };
 
@@ -196,17 +198,31 @@ us_status make_plan(int M, int K, int N, bool perm, int bits, const us_spmm_opts
             while (wpg_only > nkb) wpg_only /= 2;          // at least one LT per slice
         }
     }
-    choose_config(M, K, N, perm, bits, n_cu, wpg_only, staging, ch_only, pl.wpg, pl.cfg);
+    choose_config(M, K, N, perm, bits, n_cu, wpg_only, staging, ch_only, pl.wpg, pl.cfg, pl.gens);
     return pl.cfg < 0 ? US_ERR_ARG : US_OK;               // no configuration fits LDS
 }
 
 // Whether an automatic call takes the tile kernel (us_spmm_tile.h), which
-// runs all columns in one launch: above 16 columns, where it was the faster
-// on every shape swept (0.79 of the time at 17-32 columns, 0.25 above). A
-// forced configuration keeps the kernel family it names.
-bool use_tile(int M, int N, const us_spmm_opts *o) {
-    const bool forced = o && (o->split_k != 0 || o->variant != 0 || o->chunk_lts != 0 || o->k_blocks > 1);
-    return !forced && N > 16 && M <= kTileMaxM;
+// runs all columns in one launch. It was the faster on nearly every shape
+// swept, on average by 4x above 32 columns, 1.27x at 17-32 and 1.13x up to 16
+// (by up to 1.4x there). The chunked kernel keeps narrow calls that it runs
+// in one generation of workgroups with one chunk per wavefront where that
+// chunk fits the slice and the tile kernel's chunks of four LTs do not:
+//  - 11-LT chunks (slices of 9 to 11 LTs, three chunks of the tile kernel) up
+//    to 8 columns, or 16 with reordered or 2-bit weights: 8192x5120 N = 4
+//    5.59 against 6.01 us, 4096x11008 N = 8 6.67 against 6.83 from HBM,
+//    13552x2176 N = 2 with 2-bit weights 4.86 against 5.85;
+//  - 16-LT chunks up to 4 columns: 12288x4096 N = 4 5.98 against 6.09 us at
+//    50 % sparsity, 6.58 against 6.85 at 30 %;
+//  - 16 wavefronts of 8-LT chunks up to 8 columns: 2048x8192 N = 4 4.87
+//    against 5.05 us.
+// At 12 columns on rows in stored order all of these lose by 9 % or more.
+bool use_tile(const Plan &chunked, int K, int N, bool perm, int bits) {
+    const int nkb = K / US_LT_W, ch = kCfgs[chunked.cfg].ch;
+    if (chunked.gens != 1 || (nkb + chunked.wpg - 1) / chunked.wpg > ch) return true;
+    if (ch == 11) return !(N <= 8 || perm || bits == 2);
+    if (ch == 16) return N > 4;
+    return !(ch == 8 && chunked.wpg == 16 && N <= 8);
 }
 
 us_status check_shape(int32_t M, int32_t K, int32_t N) {
@@ -293,8 +309,14 @@ extern "C" us_status us_spmm(const us_iebme_dev *w, const uint8_t *x, int32_t N,
     a.n_cu = n_cu;
 
     hipStream_t s = (hipStream_t)stream;
-    if (use_tile(M, N, opts)) {
-        const int idx = tile_pick(M / US_LT_H, (int)nkb, N, bits, n_cu);
+    // Automatic calls of more than 16 columns, and most narrower ones, take
+    // the tile kernel; a forced configuration keeps the family it names.
+    const bool forced = opts && (opts->split_k != 0 || opts->variant != 0 || opts->chunk_lts != 0 || opts->k_blocks > 1);
+    if (!forced && M <= kTileMaxM) {
+        Plan chunked;
+        if (N <= 16 && (st = make_plan(M, K, N, perm, bits, opts, n_cu, ws != nullptr, chunked)) != US_OK) return st;
+        const int idx = N > 16 || use_tile(chunked, K, N, perm, bits)
+                            ? tile_pick(M / US_LT_H, (int)nkb, N, bits, n_cu) : -1;
         if (idx >= 0) {
             TileArgs t;
             t.a = a;

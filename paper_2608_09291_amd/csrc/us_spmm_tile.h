@@ -1,5 +1,5 @@
-// IE-BME x INT4 -> INT32 sparse product on gfx950: the tile kernel, for more
-// than 16 activation columns. Same operation and format as the chunked kernel
+// IE-BME x INT4 -> INT32 sparse product on gfx950: the tile kernel, which
+// automatic calls of every width take. Same operation and format as the chunked kernel
 // of us_spmm_kernel.h (Section VI: the UnionSparse kernel, its LSPD decode
 // and split-K); what differs:
 //
@@ -36,12 +36,13 @@
 //    64 chunks are worked out at once, one chunk per lane, so that a request
 //    is a few scalar instructions.
 //
-// Measured against the slabs of 32 columns it replaces (us per call, weights
-// 50 % sparse, before -> after): 12288x4096 N = 1024 300 -> 57, 4096x11008
-// N = 256 82 -> 25, N = 100 37 -> 16; 28672x8192 70 % sparse N = 32 37 -> 24,
-// 12288x4096 N = 32 10.1 -> 7.9. Over 686 shapes (M 256-28672, K 512-11008)
-// the choice of tile_pick runs in 0.25 of the time at N = 33-1024 and in
-// 0.79 at N = 17-32 (geometric means), and was not slower on any of them.
+// Measured against the chunked kernel (us per call, weights 50 % sparse where
+// not said, before -> after): 12288x4096 N = 1024 300 -> 57, 4096x11008
+// N = 256 82 -> 25, N = 100 37 -> 16, 28672x8192 70 % sparse N = 32 37 -> 24,
+// 13824x5120 60 % N = 16 11.2 -> 8.9, 28672x8192 70 % N = 1 20.8 -> 17.8,
+// 11008x4096 N = 8 6.8 -> 6.0, 1024x4096 N = 8 4.1 -> 3.5. Geometric means
+// over 1256 swept shapes (M 256-28672, K 512-28672) with the choice of
+// tile_pick: 0.25 of the time at N = 33-1024, 0.79 at 17-32, 0.88 at 1-16.
 #ifndef UNIONSPARSE_US_SPMM_TILE_H
 #define UNIONSPARSE_US_SPMM_TILE_H
 
@@ -60,25 +61,28 @@ struct TileCfg {
     float s, a, b, e;
 };
 
-// The built configurations. Their cost constants were fitted, one
-// configuration at a time, to the sweep described above; the list itself is
-// what a greedy choice from 43 configurations left (mean loss against the
-// fastest of all 43: 1 % at N = 17-32, 4 % above).
-#define US_TILE_CFGS(X)                                        \
-    X(1, 1, 1, 4, 1, 8, 1, 0.37f, 0.69f, 0.273f, 0.07f)        \
-    X(1, 1, 1, 8, 2, 8, 1, 0.70f, 0.62f, 0.268f, 0.00f)        \
-    X(1, 2, 1, 2, 2, 5, 1, 0.53f, 0.63f, 0.347f, 0.34f)        \
-    X(1, 2, 1, 4, 1, 5, 1, 0.37f, 0.76f, 0.363f, 0.11f)        \
-    X(1, 2, 1, 8, 2, 5, 1, 0.68f, 0.80f, 0.365f, 0.07f)        \
-    X(2, 2, 1, 4, 1, 4, 1, 0.70f, 1.03f, 0.585f, 0.22f)        \
-    X(2, 3, 1, 2, 2, 3, 1, 1.34f, 0.98f, 0.679f, 0.75f)        \
-    X(2, 3, 1, 4, 2, 3, 1, 0.67f, 0.98f, 0.672f, 0.66f)        \
-    X(2, 4, 1, 1, 2, 2, 1, 1.03f, 1.02f, 0.774f, 1.73f)        \
-    X(2, 4, 1, 4, 2, 2, 1, 0.71f, 1.08f, 0.795f, 0.80f)        \
-    X(2, 4, 1, 8, 2, 2, 1, 1.31f, 1.67f, 0.606f, 0.33f)        \
-    X(4, 4, 2, 2, 1, 2, 2, 1.67f, 2.06f, 1.268f, 2.40f)        \
-    X(2, 8, 4, 1, 1, 3, 1, 0.00f, 1.63f, 0.998f, 2.72f)        \
-    X(3, 8, 4, 1, 1, 2, 1, 0.00f, 1.99f, 1.281f, 4.11f)
+// The built configurations: what a greedy choice from 43 left. Their cost
+// constants were fitted to the sweeps described above, then refined for the
+// smallest mean loss against the fastest of all 43 (1 % at N = 1-32, 3 %
+// above).
+#define US_TILE_CFGS(X)                                            \
+    X(1, 1, 1, 2, 2, 8, 1, 0.300f, 0.554f, 0.266f, 0.318f)         \
+    X(1, 1, 1, 4, 1, 8, 1, 0.092f, 0.685f, 0.292f, 0.160f)         \
+    X(1, 1, 1, 8, 2, 8, 1, 0.380f, 0.560f, 0.266f, 0.070f)         \
+    X(1, 1, 1, 16, 2, 8, 1, 0.711f, 0.450f, 0.224f, 0.080f)        \
+    X(2, 1, 1, 4, 2, 5, 1, 1.317f, 0.660f, 0.400f, 0.080f)         \
+    X(1, 2, 1, 2, 2, 5, 1, 0.477f, 0.630f, 0.347f, 0.281f)         \
+    X(1, 2, 1, 4, 1, 5, 1, 0.370f, 0.760f, 0.363f, 0.110f)         \
+    X(1, 2, 1, 8, 2, 5, 1, 0.680f, 0.855f, 0.365f, 0.070f)         \
+    X(2, 2, 1, 4, 1, 4, 1, 0.700f, 1.030f, 0.585f, 0.220f)         \
+    X(2, 3, 1, 2, 2, 3, 1, 1.120f, 0.980f, 0.699f, 0.750f)         \
+    X(2, 3, 1, 4, 2, 3, 1, 0.637f, 0.980f, 0.727f, 0.514f)         \
+    X(2, 4, 1, 1, 2, 2, 1, 0.939f, 0.976f, 0.774f, 1.730f)         \
+    X(2, 4, 1, 4, 2, 2, 1, 0.710f, 1.044f, 0.795f, 0.800f)         \
+    X(2, 4, 1, 8, 2, 2, 1, 1.178f, 1.700f, 0.606f, 0.330f)         \
+    X(4, 4, 2, 2, 1, 2, 2, 1.898f, 2.060f, 1.426f, 2.400f)         \
+    X(2, 8, 4, 1, 1, 3, 1, 0.000f, 1.845f, 0.998f, 2.556f)         \
+    X(3, 8, 4, 1, 1, 2, 1, 0.000f, 2.028f, 1.281f, 5.387f)
 
 #define US_TILE_ROW(...) {__VA_ARGS__},
 constexpr TileCfg kTileCfgs[] = {US_TILE_CFGS(US_TILE_ROW)};
@@ -211,7 +215,7 @@ __global__ __launch_bounds__(64 * WM * WK, PERM && LW == 8 ? 7 : LW) void us_spm
 #pragma unroll
         for (int b0 = 0; b0 < 2 * C; b0 += WM) {
             const int b = b0 + wm;
-            if (2 * C % WM == 0 || b < 2 * C)
+            if ((2 * C % WM == 0 || b < 2 * C) && n0 + 8 * b < N)   // (blocks past N feed no output)
                 dma16_x(xdesc, st_x + buf * S::kXBuf + 1024u * b, v + (uint32_t)(8 * b) * xrow + (xq0 ^ (uint32_t)(16 * (b & 1))));
         }
     };
@@ -256,7 +260,7 @@ __global__ __launch_bounds__(64 * WM * WK, PERM && LW == 8 ? 7 : LW) void us_spm
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             pa0[r] = us_range::first_byte<BITS>(ob[r], (uint32_t)pay_bytes);
-            plen[r] = us_range::range_bytes32<BITS>(oe[r], pa0[r], (uint32_t)pay_bytes, (uint32_t)S::kPieces);
+            plen[r] = us_range::value_bytes<BITS>(oe[r], pa0[r], (uint32_t)pay_bytes, (uint32_t)S::kPieces);
         }
     };
     uint32_t base[R];                                         // first staged byte of the chunk being decoded
@@ -315,6 +319,12 @@ __global__ __launch_bounds__(64 * WM * WK, PERM && LW == 8 ? 7 : LW) void us_spm
     load_ranges(0);
     load_rows(0);
     load_x(0, 0);
+    // Dequant scales of this lane's rows (row 8 (rr mod 2) + rr / 2 of every
+    // row block), requested now so that the epilogue does not wait for them.
+    const uint32_t m_in = 8u * (uint32_t)(rr & 1) + (uint32_t)i;
+    float sc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) sc[r] = scale ? scale[min(rb0 + r, (uint32_t)nrb - 1u) * 16u + m_in] : 0.0f;
     for (int e = threadIdx.x; e < 256; e += 64 * WM * WK) lut[e] = perm_selectors<BITS>((uint32_t)e);
     load_payload(0, 0);
     __syncthreads();
@@ -420,13 +430,12 @@ __global__ __launch_bounds__(64 * WM * WK, PERM && LW == 8 ? 7 : LW) void us_spm
     const __amdgpu_buffer_rsrc_t fdst = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(yf + (scale ? (int64_t)n0 * m_ : 0)), (short)0, scale ? tile_bytes : 0, kBufferDword3);
     // Lane (rr, g), element v: row 8 (rr & 1) + rr / 2 of its row block, column 4 g + v.
-    const uint32_t lane_off = 4u * (uint32_t)(8 * (rr & 1) + i) + (uint32_t)(4 * g) * row4;
+    const uint32_t lane_off = 4u * m_in + (uint32_t)(4 * g) * row4;
     if constexpr (WK == 1) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (rb0 + r >= (uint32_t)nrb) break;
             const uint32_t at = lane_off + 64u * (rb0 + r);
-            const float sc = scale ? scale[(rb0 + r) * 16u + (uint32_t)(8 * (rr & 1) + i)] : 0.0f;
 #pragma unroll
             for (int cb = 0; cb < C; ++cb)
 #pragma unroll
@@ -434,13 +443,13 @@ __global__ __launch_bounds__(64 * WM * WK, PERM && LW == 8 ? 7 : LW) void us_spm
                     const int32_t yv = acc[r][cb][v] >> kShift;
                     const uint32_t o = at + (uint32_t)(16 * cb + v) * row4;
                     __builtin_amdgcn_raw_buffer_store_b32((uint32_t)yv, ydst, o, 0, 0);
-                    if (scale) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)yv * sc), fdst, o, 0, 0);
+                    if (scale) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)yv * sc[r]), fdst, o, 0, 0);
                 }
         }
     } else {
         // Split-K combine, a few 16 x 16 blocks per wavefront and round: the
         // WK partials of a block's element row (64 lanes) are summed by one
-        // wavefront.
+        // of the wavefronts that made them.
         constexpr int kPer = S::kShare < kBlocks ? S::kShare : kBlocks;
         static_assert(kPer >= 1, "a wavefront's share of the LDS holds at least one block");
         const uint32_t mine = lds0 + (uint32_t)((wm * WK + wk) * kPer) * 1024u + 4u * lane;
@@ -457,11 +466,11 @@ __global__ __launch_bounds__(64 * WM * WK, PERM && LW == 8 ? 7 : LW) void us_spm
             }
             __syncthreads();
             const int rows_now = 4 * (kBlocks - b0 < kPer ? kBlocks - b0 : kPer);
-            for (int q = wave; q < WM * rows_now; q += WM * WK) {         // wave-uniform
-                const int w = q / rows_now, bv = q % rows_now, blk = b0 + (bv >> 2), v = bv & 3;
-                const uint32_t rb = (group * WM + w) * R + blk / C;
+            for (int q = wk; q < rows_now; q += WK) {                     // wave-uniform
+                const int blk = b0 + (q >> 2), v = q & 3;
+                const uint32_t rb = rb0 + (uint32_t)(blk / C);
                 if (rb >= (uint32_t)nrb) continue;
-                const uint32_t at = lds0 + (uint32_t)(w * WK * kPer) * 1024u + (uint32_t)bv * 256u + 4u * lane;
+                const uint32_t at = lds0 + (uint32_t)(wm * WK * kPer) * 1024u + (uint32_t)q * 256u + 4u * lane;
                 int32_t s = 0;
 #pragma unroll
                 for (int k = 0; k < WK; ++k) s += (int32_t)lds_load(at + (uint32_t)(k * kPer * 1024));
@@ -469,8 +478,10 @@ __global__ __launch_bounds__(64 * WM * WK, PERM && LW == 8 ? 7 : LW) void us_spm
                 const uint32_t o = lane_off + 64u * rb + (uint32_t)(16 * (blk % C) + v) * row4;
                 __builtin_amdgcn_raw_buffer_store_b32((uint32_t)yv, ydst, o, 0, 0);
                 if (scale) {
-                    const float sc = scale[rb * 16u + (uint32_t)(8 * (rr & 1) + i)];
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)yv * sc), fdst, o, 0, 0);
+                    float f = sc[0];
+#pragma unroll
+                    for (int r = 1; r < R; ++r) f = blk / C == r ? sc[r] : f;
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)yv * f), fdst, o, 0, 0);
                 }
             }
         }
@@ -542,7 +553,8 @@ inline float tile_cost(const TileCfg &c, int nrb, int nkb, int N, int bits, int 
     return t;
 }
 
-// The configuration with the lowest cost (its index), for N > 16 columns.
+// The configuration with the lowest cost (its index), or -1 if K is too short
+// for every configuration of that width.
 inline int tile_pick(int nrb, int nkb, int N, int bits, int n_cu) {
     int best = -1;
     float cost = 0.0f;

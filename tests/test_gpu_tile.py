@@ -1,4 +1,4 @@
-"""GPU parity of the tile kernel (automatic calls above 16 activation columns).
+"""GPU parity of the tile kernel (most automatic calls).
 
 One shape per built configuration, each with ragged ends where the
 configuration has an edge: rows that do not fill a wavefront's row blocks or
@@ -18,7 +18,12 @@ pytestmark = pytest.mark.gpu
 
 # (M, K, N): row blocks x column blocks, wavefronts along M, K slices
 SHAPES = [
-    (16, 320, 17),          # 1 x 1, 1, 4; a single row block
+    (16, 192, 7),           # 1 x 1, 1, 2; a single row block, one LT in one slice
+    (16, 320, 3),           # 1 x 1, 1, 4
+    (48, 1088, 9),          # 1 x 1, 1, 8
+    (80, 6848, 12),         # 1 x 1, 1, 16
+    (12592, 2688, 9),       # 2 x 1, 1, 4
+    (16, 320, 17),          # 1 x 1, 1, 4; two column tiles
     (80, 1088, 29),         # 1 x 1, 1, 8
     (16, 128, 17),          # 1 x 2, 1, 2
     (4112, 320, 17),        # 1 x 2, 1, 4

@@ -18,12 +18,14 @@ template <int BITS> int run() {
             for (uint32_t len : {0u, 4u, 28u, 1024u, 4096u, 1u << 20, top})
                 for (uint32_t most : {66u, 130u}) {
                     const uint32_t oe = ob + len, a0 = first_byte<BITS>(ob, pay);
-                    const uint32_t got = range_bytes32<BITS>(oe, a0, pay, most);
-                    const uint32_t old = range_bytes<BITS>(oe, a0, pay, most);
-                    // Never past the payload; equal unless the run ends before it starts.
-                    if ((uint64_t)a0 + got > pay || got % 16) ++bad;
-                    if (old != 0 && got != old) ++bad;
-                    if (old == 0 && got > 16) ++bad;
+                    const uint32_t got = value_bytes<BITS>(oe, a0, pay, most);
+                    // Whole pieces up to the run's last value, at most `most`
+                    // of them, and never past the payload.
+                    const uint64_t end = (uint64_t)oe * BITS / 8;
+                    uint64_t want = end > a0 ? (end - a0 + 15) / 16 * 16 : 0;
+                    if (want > 16 * most) want = 16 * most;
+                    if (want > pay - a0) want = pay - a0;
+                    if (got != want || (uint64_t)a0 + got > pay || got % 16) ++bad;
                     ++n;
                 }
     printf("%ld of %ld bad\n", bad, n);
@@ -33,7 +35,7 @@ int main() { return run<4>() | run<2>(); }
 '''
 
 
-def test_range32_saturates_and_matches(tmp_path):
+def test_value_bytes_saturates(tmp_path):
     src = tmp_path / "r.cpp"
     src.write_text(SRC)
     exe = tmp_path / "r"
