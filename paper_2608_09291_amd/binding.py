@@ -257,10 +257,14 @@ class DeviceEncoded:
 
 def to_device(enc: Encoded, device="cuda") -> DeviceEncoded:
     import torch
-    bm = torch.from_numpy(enc.bitmaps.view(np.int64).copy()).to(device)
-    off = torch.from_numpy(enc.offsets.view(np.int32).copy()).to(device)
-    pay = torch.from_numpy(enc.payload.copy()).to(device)
-    perm = None if enc.perm is None else torch.from_numpy(enc.perm.view(np.int64).copy()).to(device)
+
+    def up(a):          # straight from the native array (copied also when device is the CPU)
+        return torch.from_numpy(a).to(device, copy=True)
+
+    bm = up(enc.bitmaps.view(np.int64))
+    off = up(enc.offsets.view(np.int32))
+    pay = up(enc.payload)
+    perm = None if enc.perm is None else up(enc.perm.view(np.int64))
     return DeviceEncoded(bm, off, pay, enc.M, enc.K, enc.n_lt, enc.n_payload, perm, enc.bits)
 
 

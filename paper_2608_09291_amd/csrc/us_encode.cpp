@@ -12,6 +12,21 @@
 
 #include "us.h"
 
+// What bounds the encoder is instructions per weight: W is read twice (45 MB
+// each for 4096x11008), a small share of the time at any host's read rate. So
+// both passes handle whole 64-element rows: one compare per 16 elements
+// instead of three tests and a branch per element, and a value compression
+// of eight rank slots per step. 4096x11008, 50 % sparse, encode and upload:
+// 15.5 ms element by element, 2.9 ms by rows (16 threads).
+// The loops use SSE2 (part of x86-64) and, where the CPU has it, BMI2;
+// US_ENCODE_PORTABLE builds the plain versions only.
+#if defined(__x86_64__) && !defined(US_ENCODE_PORTABLE)
+#include <immintrin.h>
+#define US_ENCODE_X86 1
+#else
+#define US_ENCODE_X86 0
+#endif
+
 namespace {
 
 constexpr int kAreaH = US_LT_H / US_RA;   // 8 union-mask rows
@@ -35,12 +50,77 @@ void parallel_ranges(int64_t n, F body) {
 
 inline int popcount64(uint64_t v) { return __builtin_popcountll(v); }
 
-// Value of area q at union-mask position (i, j) of an LT whose (possibly
-// reordered) rows are `rows`: area q = a * C_A + c covers rows [8a, 8a+8)
-// and columns [32c, 32c+32).
-inline int8_t area_value(const int8_t *const *rows, int q, int i, int j) {
-    const int a = q / US_CA, c = q % US_CA;
-    return rows[a * kAreaH + i][c * kAreaW + j];
+// One 64-element row of an LT: bit k of the result is set where it is
+// nonzero; `bad` collects whether any element lies outside [lo, hi].
+inline uint64_t row_mask(const int8_t *row, int lo, int hi, bool &bad) {
+#if US_ENCODE_X86
+    const __m128i zero = _mm_setzero_si128(), vlo = _mm_set1_epi8((char)lo), vhi = _mm_set1_epi8((char)hi);
+    uint64_t m = 0;
+    __m128i out = zero;
+    for (int k = 0; k < 4; ++k) {
+        const __m128i v = _mm_loadu_si128((const __m128i *)(row + 16 * k));
+        m |= (uint64_t)(uint16_t)~_mm_movemask_epi8(_mm_cmpeq_epi8(v, zero)) << (16 * k);
+        out = _mm_or_si128(out, _mm_or_si128(_mm_cmplt_epi8(v, vlo), _mm_cmpgt_epi8(v, vhi)));
+    }
+    bad |= _mm_movemask_epi8(out) != 0;
+    return m;
+#else
+    uint64_t m = 0;
+    for (int k = 0; k < US_LT_W; ++k) {
+        m |= (uint64_t)(row[k] != 0) << k;
+        bad |= row[k] < lo || row[k] > hi;
+    }
+    return m;
+#endif
+}
+
+// A row's 32 rank slots: slot j holds the values of columns j (low half) and
+// j + 32 (high half), `bits` bits each.
+inline void row_slots(const int8_t *row, int bits, uint8_t slots[kAreaW]) {
+#if US_ENCODE_X86
+    const __m128i low = _mm_set1_epi8((char)((1 << bits) - 1));
+    for (int k = 0; k < 2; ++k) {
+        const __m128i c0 = _mm_and_si128(_mm_loadu_si128((const __m128i *)(row + 16 * k)), low);
+        const __m128i c1 = _mm_and_si128(_mm_loadu_si128((const __m128i *)(row + kAreaW + 16 * k)), low);
+        // (no bit crosses into the next byte: the values have at most 4 bits)
+        _mm_storeu_si128((__m128i *)(slots + 16 * k), _mm_or_si128(c0, _mm_sll_epi16(c1, _mm_cvtsi32_si128(bits))));
+    }
+#else
+    const int low = (1 << bits) - 1;
+    for (int j = 0; j < kAreaW; ++j) slots[j] = (uint8_t)((row[j] & low) | ((row[kAreaW + j] & low) << bits));
+#endif
+}
+
+// The slots at the set bits of `mask`, in order, to dst; returns their count.
+// Up to eight bytes past them may be written.
+typedef int (*compress_fn)(const uint8_t slots[kAreaW], uint32_t mask, uint8_t *dst);
+
+int compress_plain(const uint8_t slots[kAreaW], uint32_t mask, uint8_t *dst) {
+    int n = 0;
+    for (uint32_t m = mask; m; m &= m - 1u) dst[n++] = slots[__builtin_ctz(m)];
+    return n;
+}
+
+#if US_ENCODE_X86
+__attribute__((target("bmi2,popcnt"))) int compress_bmi2(const uint8_t slots[kAreaW], uint32_t mask, uint8_t *dst) {
+    int n = 0;
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t m = (mask >> (8 * k)) & 0xFFu;
+        uint64_t v;
+        std::memcpy(&v, slots + 8 * k, 8);
+        v = _pext_u64(v, _pdep_u64(m, 0x0101010101010101ull) * 0xFFull);
+        std::memcpy(dst + n, &v, 8);
+        n += __builtin_popcount(m);
+    }
+    return n;
+}
+#endif
+
+compress_fn pick_compress() {
+#if US_ENCODE_X86
+    if (__builtin_cpu_supports("bmi2") && __builtin_cpu_supports("popcnt")) return compress_bmi2;
+#endif
+    return compress_plain;
 }
 
 // Bitmap-aware row reordering of one LT (Section V-B) for R_A = C_A = 2.
@@ -145,18 +225,6 @@ us_status encode_impl(const int8_t *w, int32_t M, int32_t K, int64_t ldw, bool r
     if (ldw < K) return US_ERR_ARG;
     if ((uint64_t)M * (uint64_t)K >= (1ull << 32)) return US_ERR_SHAPE;
 
-    // Every weight must be a signed `bits`-bit value.
-    const int lo = -(1 << (bits - 1)), hi = (1 << (bits - 1)) - 1;
-    std::atomic<bool> bad{false};
-    parallel_ranges(M, [&](int64_t r0, int64_t r1) {
-        for (int64_t r = r0; r < r1 && !bad.load(std::memory_order_relaxed); ++r) {
-            const int8_t *row = w + r * ldw;
-            for (int32_t k = 0; k < K; ++k)
-                if (row[k] < lo || row[k] > hi) { bad = true; break; }
-        }
-    });
-    if (bad) return US_ERR_RANGE;
-
     const int64_t nkb = K / US_LT_W;
     const int64_t n_lt = (int64_t)(M / US_LT_H) * nkb;
     uint64_t *bitmaps = (uint64_t *)std::calloc((size_t)n_lt * US_WORDS_PER_LT, sizeof(uint64_t));
@@ -187,10 +255,13 @@ us_status encode_impl(const int8_t *w, int32_t M, int32_t K, int64_t ldw, bool r
         }
     };
 
-    // Pass 1: row reordering (optional), then the shared union mask B_t and
-    // P_t = ||B_t||_0 per LT; count nonzeros.
+    // Pass 1: check that every weight is a signed `bits`-bit value; row
+    // reordering (optional), then the shared union mask B_t and P_t =
+    // ||B_t||_0 per LT; count nonzeros. One pass over W: a row's nonzero mask
+    // gives its count, its folded mask (Eq. 3) and its part of B_t.
+    const int lo = -(1 << (bits - 1)), hi = (1 << (bits - 1)) - 1;
     std::atomic<int64_t> nnz{0};
-    std::atomic<bool> oom{false};
+    std::atomic<bool> bad{false}, oom{false};
     parallel_ranges(n_lt, [&](int64_t t0, int64_t t1) {
         RowPairing *dp = nullptr;
         if (reorder) {
@@ -202,52 +273,42 @@ us_status encode_impl(const int8_t *w, int32_t M, int32_t K, int64_t ldw, bool r
             }
         }
         int64_t local_nnz = 0;
+        bool local_bad = false;
         for (int64_t t = t0; t < t1; ++t) {
+            const int8_t *base = w + (t / nkb) * US_LT_H * ldw + (t % nkb) * US_LT_W;
+            uint32_t fold[US_LT_H];
+            for (int r = 0; r < US_LT_H; ++r) {
+                const uint64_t m = row_mask(base + (int64_t)r * ldw, lo, hi, local_bad);
+                local_nnz += popcount64(m);
+                fold[r] = (uint32_t)m | (uint32_t)(m >> kAreaW);
+            }
+            if (local_bad) break;
+            uint8_t pi[US_LT_H];
+            for (int p = 0; p < US_LT_H; ++p) pi[p] = (uint8_t)p;
             if (dp) {
-                const int8_t *base = w + (t / nkb) * US_LT_H * ldw + (t % nkb) * US_LT_W;
-                uint32_t fold[US_LT_H];
-                for (int r = 0; r < US_LT_H; ++r) {
-                    const int8_t *row = base + (int64_t)r * ldw;
-                    uint32_t f = 0;
-                    for (int j = 0; j < kAreaW; ++j)
-                        if (row[j] != 0 || row[kAreaW + j] != 0) f |= 1u << j;
-                    fold[r] = f;
-                }
-                uint8_t pi[US_LT_H];
                 dp->solve(fold, pi);
                 uint64_t word = 0;
                 for (int p = 0; p < US_LT_H; ++p) word |= (uint64_t)pi[p] << (4 * p);
                 perm[t] = word;
             }
-            const int8_t *rows[US_LT_H];
-            lt_rows(t, rows);
             uint64_t *bm = bitmaps + t * US_WORDS_PER_LT;
             uint32_t p = 0;
-            for (int i = 0; i < kAreaH; ++i) {
-                for (int j = 0; j < kAreaW; ++j) {
-                    bool any = false;
-                    for (int q = 0; q < US_RA * US_CA; ++q) {
-                        const bool nz = area_value(rows, q, i, j) != 0;
-                        local_nnz += nz;
-                        any |= nz;
-                    }
-                    if (any) {
-                        const int L = i * kAreaW + j;   // row-major, leftmost = LSB
-                        bm[L >> 6] |= 1ull << (L & 63);
-                        ++p;
-                    }
-                }
+            for (int i = 0; i < kAreaH; ++i) {               // row-major, leftmost = LSB
+                const uint32_t u = fold[pi[i]] | fold[pi[kAreaH + i]];
+                bm[i >> 1] |= (uint64_t)u << (kAreaW * (i & 1));
+                p += (uint32_t)__builtin_popcount(u);
             }
             P[(size_t)t] = p;
         }
         delete dp;
+        if (local_bad) bad = true;
         nnz += local_nnz;
     });
-    if (oom) {
+    if (bad || oom) {
         std::free(bitmaps);
         std::free(offsets);
         std::free(perm);
-        return US_ERR_NOMEM;
+        return bad ? US_ERR_RANGE : US_ERR_NOMEM;
     }
 
     // Union Value Offsets: o_t = sum over earlier LTs of Q * P_tau.
@@ -275,24 +336,27 @@ us_status encode_impl(const int8_t *w, int32_t M, int32_t K, int64_t ldw, bool r
     // together; the paper lists each area's values in turn (o_t + q P_t +
     // rho), which holds the same values per LT. Value n takes bits
     // (n mod per_byte) * bits of byte n / per_byte. Each LT starts on a
-    // multiple of four values, so LTs never share a byte.
+    // multiple of four values, so LTs never share a byte. With C_A = 2 a rank
+    // is one slot of 2 * bits bits, and area row a's slots are the active
+    // entries of its rows' slots, in order.
+    const compress_fn compress = pick_compress();
     parallel_ranges(n_lt, [&](int64_t t0, int64_t t1) {
         for (int64_t t = t0; t < t1; ++t) {
             const int8_t *rows[US_LT_H];
             lt_rows(t, rows);
             const uint64_t *bm = bitmaps + t * US_WORDS_PER_LT;
-            const uint64_t o = offsets[t];
-            const uint64_t Pt = P[(size_t)t];
-            uint64_t rho = 0;
-            for (int L = 0; L < kAreaH * kAreaW; ++L) {
-                if (!((bm[L >> 6] >> (L & 63)) & 1)) continue;
-                const int i = L / kAreaW, j = L % kAreaW;
-                for (int q = 0; q < US_RA * US_CA; ++q) {
-                    const uint64_t n = o + (uint64_t)(q / US_CA) * US_CA * Pt + (uint64_t)US_CA * rho + (q % US_CA);
-                    const uint8_t v = (uint8_t)area_value(rows, q, i, j) & (uint8_t)((1 << bits) - 1);
-                    payload[n / per_byte] |= (uint8_t)(v << ((n % per_byte) * bits));
-                }
-                ++rho;
+            uint8_t buf[US_LT_H * kAreaW + 16], slots[kAreaW];
+            int n = 0;
+            for (int r = 0; r < US_LT_H; ++r) {               // area row 0's rows, then area row 1's
+                const int i = r % kAreaH;
+                row_slots(rows[r], bits, slots);
+                n += compress(slots, (uint32_t)(bm[i >> 1] >> (kAreaW * (i & 1))), buf + n);
+            }
+            uint8_t *dst = payload + offsets[t] / per_byte;
+            if (bits == 4) {
+                std::memcpy(dst, buf, (size_t)n);
+            } else {                                          // two slots per byte; n = 2 P_t is even
+                for (int k = 0; k < n / 2; ++k) dst[k] = (uint8_t)(buf[2 * k] | (buf[2 * k + 1] << 4));
             }
         }
     });
