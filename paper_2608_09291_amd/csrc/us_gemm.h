@@ -28,6 +28,7 @@
 
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 namespace us_gemm_detail {
 
@@ -247,14 +248,16 @@ hipError_t launch_gemm(const int8_t *w, const int8_t *x, int32_t *y, int M, int 
     using S = GemmStage<R, C, WM, WN, WK, NB>;
     auto kern = us_gemm_i8_kernel<R, C, WM, WN, WK, NB, LW>;
     // Allow more than 64 KB of dynamic LDS: once per instantiation and device.
-    static std::atomic<unsigned long long> attr_set{0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    const unsigned long long bit = 1ull << (dev & 63);
-    if (S::kTotal > 65536 && !(attr_set.load(std::memory_order_acquire) & bit)) {
-        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
-        if (e != hipSuccess) return e;
-        attr_set.fetch_or(bit, std::memory_order_release);
+    if constexpr (S::kTotal > 65536) {
+        static std::atomic<unsigned long long> attr_set{0};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+        const unsigned long long bit = 1ull << (dev & 63);
+        if (!(attr_set.load(std::memory_order_acquire) & bit)) {
+            const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+            if (e != hipSuccess) return e;
+            attr_set.fetch_or(bit, std::memory_order_release);
+        }
     }
     const int tiles = (N + S::kCols - 1) / S::kCols;
     const int64_t groups8 = ((M / 16 + WM * R - 1) / (WM * R) + 7) / 8;
@@ -266,8 +269,9 @@ hipError_t launch_gemm(const int8_t *w, const int8_t *x, int32_t *y, int M, int 
 // Cost of a configuration in us: generations of the workgroups that the CUs
 // hold, each a start s, per chunk the larger of one wavefront's latency a and
 // the busiest SIMD's share b v (v wavefronts on it), blended a little, and
-// e v for the combine and the stores.
-inline float gemm_cost(const GemmCfg &c, int64_t nrb, int nkb, int N, int n_cu) {
+// e v for the combine and the stores. (Always inlined: every call has a
+// constant configuration, which leaves two of its ten divisions.)
+__attribute__((always_inline)) inline float gemm_cost(const GemmCfg &c, int64_t nrb, int nkb, int N, int n_cu) {
     const int w = c.WM * c.WN * c.WK, lds = c.WK * c.NB * 128 * 16 * (c.R * c.WM + c.C * c.WN);
     const int64_t groups = (nrb + c.R * c.WM - 1) / (c.R * c.WM), cols = 16 * c.C * c.WN, tiles = (N + cols - 1) / cols;
     const int by_lds = kMaxLds / lds, by_regs = 4 * c.LW / w > 0 ? 4 * c.LW / w : 1;
@@ -289,20 +293,26 @@ inline float gemm_cost(const GemmCfg &c, int64_t nrb, int nkb, int N, int n_cu) 
 // The configuration with the lowest cost. Wide tiles are left out where more
 // than half of their columns would be empty; the first configuration takes
 // every shape.
-inline int gemm_pick(int64_t nrb, int nkb, int N, int n_cu) {
-    int best = 0;
-    float cost = gemm_cost(kGemmCfgs[0], nrb, nkb, N, n_cu);
-    for (int k = 1; k < kNumGemmCfgs; ++k) {
-        const GemmCfg &c = kGemmCfgs[k];
-        if (c.WK > nkb) continue;                          // at least 64 k per slice
-        if (c.C * c.WN > 1 && 16 * c.C * c.WN >= 2 * (N + 15)) continue;
+template <int... I>
+inline int gemm_pick(int64_t nrb, int nkb, int N, int n_cu, std::integer_sequence<int, I...>) {
+    int best = -1;
+    float cost = 0.0f;
+    const auto consider = [&](auto k) __attribute__((always_inline)) {
+        constexpr GemmCfg c = kGemmCfgs[decltype(k)::value];
+        if (k > 0 && c.WK > nkb) return;                   // at least 64 k per slice
+        if (k > 0 && c.C * c.WN > 1 && 16 * c.C * c.WN >= 2 * (N + 15)) return;
         const float t = gemm_cost(c, nrb, nkb, N, n_cu);
-        if (t < cost) {
+        if (best < 0 || t < cost) {
             best = k;
             cost = t;
         }
-    }
+    };
+    (consider(std::integral_constant<int, I>()), ...);
     return best;
+}
+
+inline int gemm_pick(int64_t nrb, int nkb, int N, int n_cu) {
+    return gemm_pick(nrb, nkb, N, n_cu, std::make_integer_sequence<int, kNumGemmCfgs>());
 }
 
 }  // namespace us_gemm_detail

@@ -46,6 +46,8 @@
 #ifndef UNIONSPARSE_US_SPMM_TILE_H
 #define UNIONSPARSE_US_SPMM_TILE_H
 
+#include <utility>
+
 #include "us_spmm_kernel.h"
 
 namespace us_spmm_detail {
@@ -534,8 +536,9 @@ inline int tile_lds(const TileCfg &c, int bits) {
 // CUs hold; a generation costs s, then per chunk the larger of one
 // wavefront's latency a and the busiest SIMD's share b v (v wavefronts on
 // it), blended a little as neither hides the other entirely, and e v for the
-// combine and the stores.
-inline float tile_cost(const TileCfg &c, int nrb, int nkb, int N, int bits, int n_cu) {
+// combine and the stores. (Always inlined: every call has a constant
+// configuration, which leaves two of its ten divisions.)
+__attribute__((always_inline)) inline float tile_cost(const TileCfg &c, int nrb, int nkb, int N, int bits, int n_cu) {
     const int w = c.WM * c.WK;
     const long tiles = (N + 16 * c.C - 1) / (16 * c.C), groups = (nrb + c.R * c.WM - 1) / (c.R * c.WM);
     const int by_lds = kMaxLds / tile_lds(c, bits), by_regs = 4 * c.LW / w > 0 ? 4 * c.LW / w : 1;
@@ -555,20 +558,26 @@ inline float tile_cost(const TileCfg &c, int nrb, int nkb, int N, int bits, int 
 
 // The configuration with the lowest cost (its index), or -1 if K is too short
 // for every configuration of that width.
-inline int tile_pick(int nrb, int nkb, int N, int bits, int n_cu) {
+template <int... I>
+inline int tile_pick(int nrb, int nkb, int N, int bits, int n_cu, std::integer_sequence<int, I...>) {
     int best = -1;
     float cost = 0.0f;
-    for (int k = 0; k < kNumTileCfgs; ++k) {
-        const TileCfg &c = kTileCfgs[k];
-        if (c.WK > nkb) continue;                              // at least one LT per slice
-        if (c.C > 1 && 16 * c.C >= N + 16) continue;           // a whole column block would be empty
-        const float t = tile_cost(c, nrb, nkb, N, bits, n_cu);
+    const auto consider = [&](auto k) __attribute__((always_inline)) {
+        constexpr TileCfg c = kTileCfgs[decltype(k)::value];
+        if (c.WK > nkb) return;                                // at least one LT per slice
+        if (c.C > 1 && 16 * c.C >= N + 16) return;             // a whole column block would be empty
+        const float t = bits == 2 ? tile_cost(c, nrb, nkb, N, 2, n_cu) : tile_cost(c, nrb, nkb, N, 4, n_cu);
         if (best < 0 || t < cost) {
             best = k;
             cost = t;
         }
-    }
+    };
+    (consider(std::integral_constant<int, I>()), ...);
     return best;
+}
+
+inline int tile_pick(int nrb, int nkb, int N, int bits, int n_cu) {
+    return tile_pick(nrb, nkb, N, bits, n_cu, std::make_integer_sequence<int, kNumTileCfgs>());
 }
 
 }  // namespace us_spmm_detail
