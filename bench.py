@@ -316,6 +316,21 @@ def copy_probe(torch, args, timer):
           flush=True)
 
 
+def launched(w, N: int, args) -> dict:
+    """The kernel the timed calls launch and its configuration."""
+    opts = dict(split_k=args.split_k, variant=args.variant, reordered=args.reorder, bits=args.bits,
+                chunk_lts=args.chunk_lts, k_blocks=args.k_blocks)
+    r = binding.spmm_route(w.M, w.K, N, **opts)
+    out = {"kernel": binding.KERNELS[r["kernel"]], "launches": r["launches"], "split_k": r["split_k"],
+           "chunk_lts": r["chunk_lts"], "k_blocks": 1}
+    if out["kernel"] == "us_spmm_tile_kernel":
+        out.update(staging="tile", row_blocks=r["row_blocks"], col_blocks=r["col_blocks"], waves_m=r["waves_m"])
+    else:
+        plan = binding.spmm_plan(w.M, w.K, N, full=True, **opts)
+        out.update(staging={1: "whole", 2: "ring", 3: "single pass"}[plan[2]], k_blocks=plan[3])
+    return out
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -372,8 +387,7 @@ def main():
         log(f"[bench] cpu oracle {cpu['ms_per_call']} ms/call on {cpu['cores']} threads")
 
     rep = r["rep"]
-    plan = binding.spmm_plan(w.M, w.K, N, args.split_k, args.variant, reordered=args.reorder, bits=args.bits,
-                             chunk_lts=args.chunk_lts, k_blocks=args.k_blocks, full=True)
+    plan = launched(w, N, args)
     out = {
         "metric": METRIC,
         "value": round(gbs, 2),
@@ -389,8 +403,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": w.name, "M": w.M, "K": w.K, "N": N, "sparsity": w.sparsity,
                    "dequant": w.dequant, "weight_bits": args.bits, "reordered": args.reorder,
-                   "split_k": plan[0], "chunk_lts": plan[1], "k_blocks": plan[3],
-                   "staging": {1: "whole", 2: "ring", 3: "single pass"}[plan[2]],
+                   **{k: v for k, v in plan.items() if k != "kernel"},
                    "plan": "auto" if not (args.split_k or args.variant or args.chunk_lts or args.k_blocks) else "forced",
                    "weights": f"w{args.bits}a4 IE-BME (16x64 tiles, 2x2 areas), int8 MFMA, int32 accumulate",
                    "rotating_copies": r["n_copies"]},
@@ -408,7 +421,7 @@ def main():
                      "traffic": (measured_traffic(w.name, N, args.reorder)
                                  if args.bits == 4 and not (args.split_k or args.variant or args.chunk_lts
                                                             or args.k_blocks) else None),
-                     "kernel": "us_spmm_kernel",
+                     "kernel": plan["kernel"],
                      "bytes_per_launch": r["alg_bytes"]},
         "cpu_baseline": cpu,
         **extras,

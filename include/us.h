@@ -265,11 +265,38 @@ typedef struct {
  * options can force, which automatic us_spmm calls use for some narrow
  * shapes; the others take the tile kernel (one launch for all columns) in a
  * configuration chosen by its own cost model, which these fields do not
- * describe. Host only; for tuning and reporting.
+ * describe (us_spmm_route does). Host only; for tuning and reporting.
  * Same argument errors as us_spmm; US_ERR_ARG if no configuration fits.
  */
 us_status us_spmm_plan(int32_t M, int32_t K, int32_t N, int32_t bits, int32_t reordered, const us_spmm_opts *opts,
                        int32_t *split_k, int32_t *chunk_lts, int32_t *staging, int32_t *k_blocks);
+
+/* Kernels of us_spmm (us_spmm_route_info.kernel). */
+#define US_KERNEL_CHUNKED 1 /* a row block per workgroup, in chunks of LTs  */
+#define US_KERNEL_BURST 2   /* the same, every slice requested at once      */
+#define US_KERNEL_TILE 3    /* several row and column blocks per wavefront  */
+
+typedef struct {
+    int32_t kernel;
+    int32_t launches;   /* 1, or one per slab of US_N_MAX columns          */
+    int32_t row_blocks; /* blocks of 16 rows per wavefront                 */
+    int32_t col_blocks; /* blocks of 16 columns per wavefront              */
+    int32_t waves_m;    /* wavefronts of a K slice, along M                */
+    int32_t split_k;    /* K slices per workgroup                          */
+    int32_t chunk_lts;  /* LTs of a row block per chunk or slice           */
+} us_spmm_route_info;
+
+/*
+ * us_spmm_route - the kernel and configuration that an us_spmm call of this
+ * shape, weight form and options launches on the current device (a 256-CU
+ * MI355X when no device is visible), given a workspace; for a call of
+ * several slabs those of the first. Unlike us_spmm_plan it covers every
+ * kernel of automatic calls (the paper's shape-aware kernel selection,
+ * Section I, contributions). Host only; for reporting and tests.
+ * Same argument errors as us_spmm_plan.
+ */
+us_status us_spmm_route(int32_t M, int32_t K, int32_t N, int32_t bits, int32_t reordered, const us_spmm_opts *opts,
+                        us_spmm_route_info *out);
 
 /*
  * us_spmm_workspace_size - device workspace bytes us_spmm needs for this

@@ -25,8 +25,8 @@ N_LIMIT = 1024      # widest activation matrix (slabs of N_MAX beyond N_MAX)
 K_MAX = 130048
 
 #: Every symbol the two public headers declare.
-EXPORTS = ("us_encode", "us_encode_w2", "us_encode_reordered", "us_iebme_free", "us_pmr", "us_pmr_formats", "us_spmm_plan", "us_spmm_workspace_size", "us_spmm", "us_spmm_noalloc",
-           "us_gemm_i8", "us_status_string", "us_probe_read", "us_probe_read_sink_words",
+EXPORTS = ("us_encode", "us_encode_w2", "us_encode_reordered", "us_iebme_free", "us_pmr", "us_pmr_formats", "us_spmm_plan", "us_spmm_route",
+           "us_spmm_workspace_size", "us_spmm", "us_spmm_noalloc", "us_gemm_i8", "us_status_string", "us_probe_read", "us_probe_read_sink_words",
            "us_probe_copy", "us_probe_copy_lds", "us_probe_spin")
 
 
@@ -79,6 +79,16 @@ class SpmmOpts(ctypes.Structure):
                 ("k_blocks", ctypes.c_int32)]
 
 
+#: us_spmm_route_info.kernel values, as the kernels' names
+KERNELS = {1: "us_spmm_kernel", 2: "us_spmm_burst_kernel", 3: "us_spmm_tile_kernel"}
+
+
+class RouteInfo(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int32), ("launches", ctypes.c_int32), ("row_blocks", ctypes.c_int32),
+                ("col_blocks", ctypes.c_int32), ("waves_m", ctypes.c_int32), ("split_k", ctypes.c_int32),
+                ("chunk_lts", ctypes.c_int32)]
+
+
 #: us_spmm_opts.variant values
 VARIANT_AUTO, VARIANT_WHOLE, VARIANT_RING, VARIANT_BURST = 0, 1, 2, 3
 K_BLOCKS_MAX = 64   # US_K_BLOCKS_MAX
@@ -106,6 +116,7 @@ def lib():
                                              ctypes.POINTER(sz)]
         pi32 = ctypes.POINTER(i32)
         L.us_spmm_plan.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(SpmmOpts), pi32, pi32, pi32, pi32]
+        L.us_spmm_route.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(SpmmOpts), ctypes.POINTER(RouteInfo)]
         L.us_spmm.argtypes = [ctypes.POINTER(IEBMEDev), vp, i32, vp, vp, vp, vp, sz,
                               ctypes.POINTER(SpmmOpts), vp]
         L.us_spmm_noalloc.argtypes = [ctypes.POINTER(IEBMEDev), vp, i32, vp, vp, vp, ctypes.POINTER(SpmmOpts), vp]
@@ -118,7 +129,7 @@ def lib():
         L.us_probe_copy.argtypes = [vp, vp, sz, vp]
         L.us_probe_copy_lds.argtypes = [vp, vp, sz, vp]
         L.us_probe_spin.argtypes = [ctypes.c_uint64, vp]
-        for name in ("us_encode", "us_encode_w2", "us_encode_reordered", "us_pmr", "us_pmr_formats", "us_spmm_workspace_size", "us_spmm_plan", "us_spmm", "us_spmm_noalloc", "us_gemm_i8",
+        for name in ("us_encode", "us_encode_w2", "us_encode_reordered", "us_pmr", "us_pmr_formats", "us_spmm_workspace_size", "us_spmm_plan", "us_spmm_route", "us_spmm", "us_spmm_noalloc", "us_gemm_i8",
                      "us_probe_read", "us_probe_copy", "us_probe_copy_lds", "us_probe_spin"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
@@ -294,6 +305,15 @@ def spmm_plan(M: int, K: int, N: int, split_k: int = 0, variant: int = 0, reorde
     _check("us_spmm_plan", lib().us_spmm_plan(M, K, N, bits, int(bool(reordered)), ctypes.byref(opts),
                                               ctypes.byref(a), ctypes.byref(b), ctypes.byref(c), ctypes.byref(d)))
     return (a.value, b.value, c.value, d.value) if full else (a.value, b.value, c.value)
+
+
+def spmm_route(M: int, K: int, N: int, split_k: int = 0, variant: int = 0, reordered: bool = False, bits: int = 4,
+               chunk_lts: int = 0, k_blocks: int = 0) -> dict:
+    """us_spmm_route: the kernel a us_spmm call launches and its configuration."""
+    opts, r = SpmmOpts(split_k, variant, chunk_lts, k_blocks), RouteInfo()
+    _check("us_spmm_route", lib().us_spmm_route(M, K, N, bits, int(bool(reordered)), ctypes.byref(opts),
+                                                ctypes.byref(r)))
+    return {name: getattr(r, name) for name, _ in RouteInfo._fields_}
 
 
 def spmm(w: DeviceEncoded, x_packed, N: int, y, scale=None, y_f32=None, split_k: int = 0,

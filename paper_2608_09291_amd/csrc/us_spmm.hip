@@ -225,6 +225,33 @@ bool use_tile(const Plan &chunked, int K, int N, bool perm, int bits) {
     return !(ch == 8 && chunked.wpg == 16 && N <= 8);
 }
 
+// What a call launches: the tile kernel in configuration `tile`, or (tile < 0)
+// one launch per slab of up to US_N_MAX columns: every full slab shares one
+// plan, a narrower last slab gets its own.
+struct Call {
+    int tile = -1;
+    int n_full = 0, n_last = 0;
+    Plan full, last;
+};
+
+// Automatic calls of more than 16 columns, and most narrower ones, take the
+// tile kernel where it has a configuration for the shape (with K = 64 only
+// above 48 columns); a forced configuration keeps the family it names.
+us_status plan_call(int M, int K, int N, bool perm, int bits, const us_spmm_opts *opts, int n_cu, bool ws_ok, Call &c) {
+    us_status st;
+    const bool forced = opts && (opts->split_k != 0 || opts->variant != 0 || opts->chunk_lts != 0 || opts->k_blocks > 1);
+    c.n_full = std::min<int>(N, US_N_MAX);
+    c.n_last = N % US_N_MAX == 0 ? c.n_full : N % US_N_MAX;
+    if (!forced && M <= kTileMaxM) {
+        Plan chunked;
+        if (N <= 16 && (st = make_plan(M, K, N, perm, bits, opts, n_cu, ws_ok, chunked)) != US_OK) return st;
+        if (N > 16 || use_tile(chunked, K, N, perm, bits)) c.tile = tile_pick(M / US_LT_H, K / US_LT_W, N, bits, n_cu);
+        if (c.tile >= 0) return US_OK;
+    }
+    if ((st = make_plan(M, K, c.n_full, perm, bits, opts, n_cu, ws_ok, c.full)) != US_OK) return st;
+    return make_plan(M, K, c.n_last, perm, bits, opts, n_cu, ws_ok, c.last);
+}
+
 us_status check_shape(int32_t M, int32_t K, int32_t N) {
     if (M <= 0 || K <= 0 || M % US_LT_H || K % US_LT_W || K > US_K_MAX) return US_ERR_SHAPE;
     if ((uint64_t)M * (uint64_t)K >= (1ull << 32)) return US_ERR_SHAPE;
@@ -256,6 +283,27 @@ extern "C" us_status us_spmm_plan(int32_t M, int32_t K, int32_t N, int32_t bits,
         *staging = kCfgs[pl.cfg].ring ? kVariantRing : kVariantWhole;
     }
     if (k_blocks) *k_blocks = pl.burst ? pl.b.kblocks : 1;
+    return US_OK;
+}
+
+extern "C" us_status us_spmm_route(int32_t M, int32_t K, int32_t N, int32_t bits, int32_t reordered,
+                                   const us_spmm_opts *opts, us_spmm_route_info *out) {
+    if (!out || (bits != 4 && bits != 2) || (bits == 2 && reordered)) return US_ERR_ARG;
+    us_status st = check_shape(M, K, N);
+    if (st != US_OK) return st;
+    if ((st = check_opts(opts)) != US_OK) return st;
+    Call c;
+    st = plan_call(M, K, N, reordered != 0, bits, opts, us_device::compute_units(), true, c);
+    if (st != US_OK) return st;
+    if (c.tile >= 0) {
+        const TileCfg &t = kTileCfgs[c.tile];
+        *out = us_spmm_route_info{US_KERNEL_TILE, 1, t.R, t.C, t.WM, t.WK, 4};
+    } else {
+        *out = us_spmm_route_info{c.full.burst ? US_KERNEL_BURST : US_KERNEL_CHUNKED,
+                                  (N + US_N_MAX - 1) / US_N_MAX, 1, c.n_full > 16 ? 2 : 1, 1,
+                                  c.full.burst ? c.full.b.wpg : c.full.wpg,
+                                  c.full.burst ? c.full.b.ch : kCfgs[c.full.cfg].ch};
+    }
     return US_OK;
 }
 
@@ -309,47 +357,34 @@ extern "C" us_status us_spmm(const us_iebme_dev *w, const uint8_t *x, int32_t N,
     a.n_cu = n_cu;
 
     hipStream_t s = (hipStream_t)stream;
-    // Automatic calls of more than 16 columns, and most narrower ones, take
-    // the tile kernel; a forced configuration keeps the family it names.
-    const bool forced = opts && (opts->split_k != 0 || opts->variant != 0 || opts->chunk_lts != 0 || opts->k_blocks > 1);
-    if (!forced && M <= kTileMaxM) {
-        Plan chunked;
-        if (N <= 16 && (st = make_plan(M, K, N, perm, bits, opts, n_cu, ws != nullptr, chunked)) != US_OK) return st;
-        const int idx = N > 16 || use_tile(chunked, K, N, perm, bits)
-                            ? tile_pick(M / US_LT_H, (int)nkb, N, bits, n_cu) : -1;
-        if (idx >= 0) {
-            TileArgs t;
-            t.a = a;
-            t.a.x = x;
-            t.a.y = y;
-            t.a.yf = y_f32;
-            t.a.N = N;
-            t.nrb = M / US_LT_H;
-            t.n_tiles = (N + 16 * kTileCfgs[idx].C - 1) / (16 * kTileCfgs[idx].C);
-            const hipError_t err = bits == 2 ? launch_tile_w2(idx, t, s)
-                                   : perm    ? launch_tile_perm(idx, t, s)
-                                             : launch_tile_plain(idx, t, s);
-            return err == hipSuccess ? US_OK : US_ERR_DEVICE;
-        }
+    // Everything is planned before anything is launched.
+    Call call;
+    if ((st = plan_call(M, K, N, perm, bits, opts, n_cu, ws != nullptr, call)) != US_OK) return st;
+    if (call.tile >= 0) {
+        TileArgs t;
+        t.a = a;
+        t.a.x = x;
+        t.a.y = y;
+        t.a.yf = y_f32;
+        t.a.N = N;
+        t.nrb = M / US_LT_H;
+        t.n_tiles = (N + 16 * kTileCfgs[call.tile].C - 1) / (16 * kTileCfgs[call.tile].C);
+        const hipError_t err = bits == 2 ? launch_tile_w2(call.tile, t, s)
+                               : perm    ? launch_tile_perm(call.tile, t, s)
+                                         : launch_tile_plain(call.tile, t, s);
+        return err == hipSuccess ? US_OK : US_ERR_DEVICE;
     }
 
-    // Slabs of up to US_N_MAX columns: every full slab shares one plan, a
-    // narrower last slab gets its own. Both are made before anything is
-    // launched. A split across workgroups needs the workspace for the
-    // slab's columns.
-    const int n_full = std::min<int>(N, US_N_MAX), n_last = N % US_N_MAX == 0 ? n_full : N % US_N_MAX;
-    Plan p_full, p_last;
-    if ((st = make_plan(M, K, n_full, perm, bits, opts, n_cu, ws != nullptr, p_full)) != US_OK) return st;
-    if ((st = make_plan(M, K, n_last, perm, bits, opts, n_cu, ws != nullptr, p_last)) != US_OK) return st;
-    for (const Plan *pl : {&p_full, &p_last}) {
+    // A split across workgroups needs the workspace for the slab's columns.
+    for (const Plan *pl : {&call.full, &call.last}) {
         if (pl->burst && pl->b.kblocks > 1 &&
-            (ws == nullptr || ws_bytes < burst_ws_bytes(pl->b.kblocks, M, pl == &p_full ? n_full : n_last)))
+            (ws == nullptr || ws_bytes < burst_ws_bytes(pl->b.kblocks, M, pl == &call.full ? call.n_full : call.n_last)))
             return US_ERR_ARG;
     }
 
     for (int n0 = 0; n0 < N; n0 += US_N_MAX) {
         const int ns = std::min(US_N_MAX, N - n0);
-        const Plan &pl = ns == n_full ? p_full : p_last;
+        const Plan &pl = ns == call.n_full ? call.full : call.last;
         a.x = x + (int64_t)n0 * (K / 2);
         a.y = y + (int64_t)n0 * M;
         a.yf = y_f32 ? y_f32 + (int64_t)n0 * M : nullptr;

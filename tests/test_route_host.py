@@ -1,0 +1,70 @@
+"""us_spmm_route: the kernel a us_spmm call launches (host only; 256 compute units when no GPU is visible)."""
+import argparse
+import ctypes
+
+import pytest
+
+import bench
+from paper_2608_09291_amd import binding, synth
+
+FORMS = [(4, False), (4, True), (2, False)]
+
+
+@pytest.mark.parametrize("M,K,N,kernel,launches", [
+    (4096, 11008, 8, "us_spmm_kernel", 1),             # a narrow call in one chunk per wavefront
+    (28672, 8192, 1, "us_spmm_tile_kernel", 1),
+    (28672, 8192, 32, "us_spmm_tile_kernel", 1),
+    (12288, 4096, 1024, "us_spmm_tile_kernel", 1),
+    (4096, 64, 40, "us_spmm_kernel", 2),               # one LT per row block: no tile of that width
+    (4096, 64, 49, "us_spmm_tile_kernel", 1),
+    ((1 << 22) + 16, 64, 1024, "us_spmm_kernel", 32),  # Y beyond the tile kernel's offsets
+])
+def test_kernel_of_automatic_calls(M, K, N, kernel, launches):
+    r = binding.spmm_route(M, K, N)
+    assert (binding.KERNELS[r["kernel"]], r["launches"]) == (kernel, launches)
+
+
+@pytest.mark.parametrize("bits,reordered", FORMS)
+def test_agrees_with_the_plan_off_the_tile_kernel(bits, reordered):
+    chunked = 0
+    for M, K in ((16, 64), (512, 512), (1024, 4096), (4096, 11008), (12288, 4096), (48, 130048)):
+        for N in (1, 4, 8, 12, 16, 17, 32, 33):
+            for opts in ({}, {"split_k": 2, "chunk_lts": 4}, {"variant": 1}, {"split_k": 4, "variant": 3}):
+                try:
+                    plan = binding.spmm_plan(M, K, N, bits=bits, reordered=reordered, **opts)
+                except binding.UsError as e:
+                    with pytest.raises(binding.UsError) as e2:
+                        binding.spmm_route(M, K, N, bits=bits, reordered=reordered, **opts)
+                    assert e2.value.status == e.status
+                    continue
+                r = binding.spmm_route(M, K, N, bits=bits, reordered=reordered, **opts)
+                if binding.KERNELS[r["kernel"]] == "us_spmm_tile_kernel":
+                    assert not opts and r["launches"] == 1 and r["split_k"] <= K // 64
+                    continue
+                chunked += 1
+                assert (r["split_k"], r["chunk_lts"]) == plan[:2]
+                assert (binding.KERNELS[r["kernel"]] == "us_spmm_burst_kernel") == (plan[2] == 3)
+                assert r["launches"] == -(-N // 32) and r["col_blocks"] == (2 if N > 16 else 1)
+    assert chunked > 0
+
+
+def test_argument_errors():
+    L, ok, out = binding.lib(), ctypes.byref(binding.SpmmOpts()), ctypes.byref(binding.RouteInfo())
+    assert L.us_spmm_route(32, 128, 8, 4, 0, None, out) == 0
+    assert L.us_spmm_route(32, 128, 8, 4, 0, ok, None) == -1
+    assert L.us_spmm_route(32, 128, 8, 3, 0, ok, out) == -1
+    assert L.us_spmm_route(32, 128, 8, 2, 1, ok, out) == -1
+    assert L.us_spmm_route(40, 128, 8, 4, 0, ok, out) == -2
+    assert L.us_spmm_route(32, 128, 1025, 4, 0, ok, out) == -2
+    assert L.us_spmm_route(32, 128, 8, 4, 0, ctypes.byref(binding.SpmmOpts(3)), out) == -1
+
+
+@pytest.mark.parametrize("workload,N,kernel", [("ffn_down_4096x11008_s50", 8, "us_spmm_kernel"),
+                                               ("ffn_28672x8192_s70", 32, "us_spmm_tile_kernel")])
+def test_bench_reports_the_kernel_it_times(workload, N, kernel):
+    args = argparse.Namespace(split_k=0, variant=0, reorder=False, bits=4, chunk_lts=0, k_blocks=0)
+    w = synth.WORKLOADS[workload]
+    out = bench.launched(w, N, args)
+    r = binding.spmm_route(w.M, w.K, N)
+    assert out["kernel"] == kernel and out["split_k"] == r["split_k"] and out["chunk_lts"] == r["chunk_lts"]
+    assert (out["staging"] == "tile") == (kernel == "us_spmm_tile_kernel")
