@@ -1,6 +1,7 @@
 """us_spmm_route: the kernel a us_spmm call launches (host only; 256 compute units when no GPU is visible)."""
 import argparse
 import ctypes
+import time
 
 import pytest
 
@@ -68,3 +69,33 @@ def test_bench_reports_the_kernel_it_times(workload, N, kernel):
     r = binding.spmm_route(w.M, w.K, N)
     assert out["kernel"] == kernel and out["split_k"] == r["split_k"] and out["chunk_lts"] == r["chunk_lts"]
     assert (out["staging"] == "tile") == (kernel == "us_spmm_tile_kernel")
+
+
+def test_narrow_calls_search_for_a_plan_once():
+    """Routing a narrow call and planning its launch share one search over
+    the chunked configurations: the route costs about what us_spmm_plan
+    (one search) does, not two or three times as much."""
+    L, out = binding.lib(), binding.RouteInfo()
+    a, b, c = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+    ra, rb, rc, ro = ctypes.byref(a), ctypes.byref(b), ctypes.byref(c), ctypes.byref(out)
+
+    def best(call):
+        times = []
+        for _ in range(30):
+            t = time.perf_counter()
+            for _ in range(200):
+                call()
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    for M, K, N in ((4096, 11008, 8), (2048, 8192, 4)):
+        assert binding.KERNELS[binding.spmm_route(M, K, N)["kernel"]] == "us_spmm_kernel"
+        ratios = []
+        for _ in range(8):                                 # (one quiet attempt shows it on a busy host)
+            search, route = (best(lambda: f(M)) - best(lambda: f(40))      # M = 40 is refused before the search
+                             for f in (lambda m: L.us_spmm_plan(m, K, N, 4, 0, None, ra, rb, rc, None),
+                                       lambda m: L.us_spmm_route(m, K, N, 4, 0, None, ro)))
+            ratios.append(route / search if search > 0 else float("inf"))
+            if ratios[-1] < 1.5:
+                break
+        assert ratios[-1] < 1.5, (M, K, N, ratios)
