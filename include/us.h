@@ -373,7 +373,8 @@ us_status us_spmm_noalloc(const us_iebme_dev *w, const uint8_t *x, int32_t N, in
  *   x : device int8, N x K row-major (row n is activation column n), 16-byte aligned
  *   y : device int32, N x M row-major
  * M % 16 == 0, K % 64 == 0, K <= US_K_MAX, 1 <= N <= US_N_LIMIT. One launch
- * for all columns; under HIP graph capture the rule of us_spmm applies.
+ * for all columns, which can be captured in a HIP graph, also by the first
+ * call of a shape (what it sets, an LDS limit, is no stream operation).
  */
 us_status us_gemm_i8(const int8_t *w, const int8_t *x, int32_t M, int32_t K, int32_t N,
                      int32_t *y, void *stream);

@@ -33,6 +33,43 @@ SHAPES = [
 ]
 
 
+# More than 64 KB of LDS (4 x 4 blocks, 8 slices; its limit is set by the
+# first call), less of it, and several wavefronts sharing it.
+CAPTURED = [(7024, 704, 100), (16, 320, 21), (8208, 704, 200)]
+
+
+def test_captured(torch_cuda):
+    """Calls captured in a graph before any other call of their shapes, and
+    replayed on changed activations, with eager calls between the replays."""
+    torch = torch_cuda
+    rng = np.random.default_rng(5)
+    calls, ref = [], []
+    for M, K, N in CAPTURED:
+        announce(f"gemm captured M={M} K={K} N={N}")
+        W = rng.integers(-128, 128, size=(M, K), dtype=np.int8)
+        Xts = [rng.integers(-128, 128, size=(N, K), dtype=np.int8) for _ in range(3)]
+        w, x = torch.from_numpy(W).cuda(), torch.from_numpy(Xts[0]).cuda()
+        calls.append((w, x, M, K, N, torch.full((N, M), -7, dtype=torch.int32, device="cuda"), Xts))
+        ref.append([product.to_int32(product.matmul_c(W, Xt)) for Xt in Xts])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for w, x, M, K, N, y, _ in calls:
+            binding.gemm_i8(w, x, M, K, N, y)
+    for i in range(3):
+        for _, x, _, _, _, y, Xts in calls:
+            x.copy_(torch.from_numpy(Xts[i]))
+            y.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        for (w, x, M, K, N, y, _), r in zip(calls, ref):
+            assert np.array_equal(y.cpu().numpy().T, r[i]), (i, M, K, N)
+            y.fill_(-7)
+            binding.gemm_i8(w, x, M, K, N, y)
+            torch.cuda.synchronize()
+            assert np.array_equal(y.cpu().numpy().T, r[i]), (i, M, K, N)
+
+
 @pytest.mark.parametrize("M,K,N", SHAPES)
 def test_every_configuration(torch_cuda, M, K, N):
     torch = torch_cuda
