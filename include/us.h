@@ -379,6 +379,22 @@ us_status us_spmm_noalloc(const us_iebme_dev *w, const uint8_t *x, int32_t N, in
 us_status us_gemm_i8(const int8_t *w, const int8_t *x, int32_t M, int32_t K, int32_t N,
                      int32_t *y, void *stream);
 
+typedef struct {
+    int32_t row_blocks; /* blocks of 16 rows per wavefront                 */
+    int32_t col_blocks; /* blocks of 16 columns per wavefront              */
+    int32_t waves_m;    /* wavefronts of a K slice along M                 */
+    int32_t waves_n;    /* and along N                                     */
+    int32_t split_k;    /* K slices per workgroup                          */
+} us_gemm_i8_route_info;
+
+/*
+ * us_gemm_i8_route - the configuration that us_gemm_i8 launches for a shape
+ * on the current device (a 256-CU MI355X when no device is visible). Host
+ * only; for reporting and tests. US_ERR_ARG without out, US_ERR_SHAPE as
+ * us_gemm_i8.
+ */
+us_status us_gemm_i8_route(int32_t M, int32_t K, int32_t N, us_gemm_i8_route_info *out);
+
 /* us_status_string - static text naming a status code. */
 const char *us_status_string(us_status s);
 

@@ -26,7 +26,7 @@ K_MAX = 130048
 
 #: Every symbol the two public headers declare.
 EXPORTS = ("us_encode", "us_encode_w2", "us_encode_reordered", "us_iebme_free", "us_pmr", "us_pmr_formats", "us_spmm_plan", "us_spmm_route",
-           "us_spmm_workspace_size", "us_spmm", "us_spmm_noalloc", "us_gemm_i8", "us_status_string", "us_probe_read", "us_probe_read_sink_words",
+           "us_spmm_workspace_size", "us_spmm", "us_spmm_noalloc", "us_gemm_i8", "us_gemm_i8_route", "us_status_string", "us_probe_read", "us_probe_read_sink_words",
            "us_probe_copy", "us_probe_copy_lds", "us_probe_spin")
 
 
@@ -89,6 +89,11 @@ class RouteInfo(ctypes.Structure):
                 ("chunk_lts", ctypes.c_int32)]
 
 
+class GemmRouteInfo(ctypes.Structure):
+    _fields_ = [("row_blocks", ctypes.c_int32), ("col_blocks", ctypes.c_int32), ("waves_m", ctypes.c_int32),
+                ("waves_n", ctypes.c_int32), ("split_k", ctypes.c_int32)]
+
+
 #: us_spmm_opts.variant values
 VARIANT_AUTO, VARIANT_WHOLE, VARIANT_RING, VARIANT_BURST = 0, 1, 2, 3
 K_BLOCKS_MAX = 64   # US_K_BLOCKS_MAX
@@ -121,6 +126,7 @@ def lib():
                               ctypes.POINTER(SpmmOpts), vp]
         L.us_spmm_noalloc.argtypes = [ctypes.POINTER(IEBMEDev), vp, i32, vp, vp, vp, ctypes.POINTER(SpmmOpts), vp]
         L.us_gemm_i8.argtypes = [vp, vp, i32, i32, i32, vp, vp]
+        L.us_gemm_i8_route.argtypes = [i32, i32, i32, ctypes.POINTER(GemmRouteInfo)]
         L.us_status_string.argtypes = [ctypes.c_int]
         L.us_status_string.restype = ctypes.c_char_p
         L.us_probe_read.argtypes = [vp, sz, vp, ctypes.c_int32, vp]
@@ -130,7 +136,7 @@ def lib():
         L.us_probe_copy_lds.argtypes = [vp, vp, sz, vp]
         L.us_probe_spin.argtypes = [ctypes.c_uint64, vp]
         for name in ("us_encode", "us_encode_w2", "us_encode_reordered", "us_pmr", "us_pmr_formats", "us_spmm_workspace_size", "us_spmm_plan", "us_spmm_route", "us_spmm", "us_spmm_noalloc", "us_gemm_i8",
-                     "us_probe_read", "us_probe_copy", "us_probe_copy_lds", "us_probe_spin"):
+                     "us_gemm_i8_route", "us_probe_read", "us_probe_copy", "us_probe_copy_lds", "us_probe_spin"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -350,6 +356,13 @@ def gemm_i8(w, x, M: int, K: int, N: int, y, stream=None) -> None:
     """us_gemm_i8: dense int8 (M, K) times int8 (N, K)^T into int32 (N, M)."""
     _check("us_gemm_i8", lib().us_gemm_i8(w.data_ptr(), x.data_ptr(), M, K, N, y.data_ptr(),
                                           _stream_handle(stream)))
+
+
+def gemm_i8_route(M: int, K: int, N: int) -> dict:
+    """us_gemm_i8_route: the configuration us_gemm_i8 launches."""
+    r = GemmRouteInfo()
+    _check("us_gemm_i8_route", lib().us_gemm_i8_route(M, K, N, ctypes.byref(r)))
+    return {name: getattr(r, name) for name, _ in GemmRouteInfo._fields_}
 
 
 PROBE_READ_SHAPES = 4      # US_PROBE_READ_SHAPES

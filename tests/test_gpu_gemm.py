@@ -1,8 +1,9 @@
 """GPU parity of every built configuration of the dense INT8 GEMM.
 
 The shapes are chosen so that the automatic choice takes the configuration
-named beside them on a 256-CU GPU, with rows, columns and k that do not fill
-its tiles, chunks or slices. Results are exact.
+given with them on a 256-CU GPU (test_route_host.py and, on such a GPU, the
+test below assert it), with rows, columns and k that do not fill its tiles,
+chunks or slices. Results are exact.
 """
 import numpy as np
 import pytest
@@ -13,23 +14,24 @@ from test_gpu_spmm import announce, torch_cuda  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
+# M, K, N, (row blocks, column blocks, wavefronts along M, along N, K slices)
 SHAPES = [
-    (48, 64, 4),          # 1 x 1 blocks, 1 x 1 wavefronts, 1 slices
-    (16, 576, 4),         # 1 x 1 blocks, 1 x 1 wavefronts, 8 slices
-    (16, 320, 21),        # 1 x 1 blocks, 1 x 1 wavefronts, 4 slices
-    (4528, 320, 1),       # 2 x 1 blocks, 1 x 1 wavefronts, 4 slices
-    (5584, 2752, 1),      # 2 x 1 blocks, 1 x 1 wavefronts, 8 slices
-    (4112, 320, 17),      # 2 x 2 blocks, 1 x 1 wavefronts, 4 slices
-    (4208, 576, 18),      # 2 x 2 blocks, 1 x 1 wavefronts, 8 slices
-    (8880, 832, 17),      # 4 x 2 blocks, 1 x 1 wavefronts, 4 slices
-    (9808, 1600, 17),     # 4 x 2 blocks, 1 x 1 wavefronts, 8 slices
-    (10032, 448, 132),    # 4 x 4 blocks, 1 x 1 wavefronts, 4 slices
-    (7024, 704, 100),     # 4 x 4 blocks, 1 x 1 wavefronts, 8 slices
-    (10704, 64, 98),      # 2 x 4 blocks, 2 x 2 wavefronts, 1 slices
-    (8464, 64, 652),      # 4 x 4 blocks, 2 x 2 wavefronts, 1 slices
-    (8208, 704, 200),     # 2 x 4 blocks, 2 x 2 wavefronts, several chunks
-    (12304, 704, 500),    # 4 x 4 blocks, 2 x 2 wavefronts, several chunks
-    (48, 130048, 3),      # the longest k
+    (48, 64, 4, (1, 1, 1, 1, 1)),
+    (16, 576, 4, (1, 1, 1, 1, 8)),
+    (16, 320, 21, (1, 1, 1, 1, 4)),
+    (4528, 320, 1, (2, 1, 1, 1, 4)),
+    (5584, 2752, 1, (2, 1, 1, 1, 8)),
+    (4112, 320, 17, (2, 2, 1, 1, 4)),
+    (4208, 576, 18, (2, 2, 1, 1, 8)),
+    (8880, 832, 17, (4, 2, 1, 1, 4)),
+    (9808, 1600, 17, (4, 2, 1, 1, 8)),
+    (10032, 448, 132, (4, 4, 1, 1, 4)),
+    (7024, 704, 100, (4, 4, 1, 1, 8)),
+    (10704, 64, 98, (2, 4, 2, 2, 1)),
+    (8464, 64, 652, (4, 4, 2, 2, 1)),
+    (8208, 704, 200, (2, 4, 2, 2, 1)),      # several chunks
+    (12304, 704, 500, (4, 4, 2, 2, 1)),     # several chunks
+    (48, 130048, 3, (1, 1, 1, 1, 8)),       # the longest k
 ]
 
 
@@ -70,10 +72,12 @@ def test_captured(torch_cuda):
             assert np.array_equal(y.cpu().numpy().T, r[i]), (i, M, K, N)
 
 
-@pytest.mark.parametrize("M,K,N", SHAPES)
-def test_every_configuration(torch_cuda, M, K, N):
+@pytest.mark.parametrize("M,K,N,cfg", SHAPES)
+def test_every_configuration(torch_cuda, M, K, N, cfg):
     torch = torch_cuda
     announce(f"gemm M={M} K={K} N={N}")
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert tuple(binding.gemm_i8_route(M, K, N).values()) == cfg
     rng = np.random.default_rng(M + K + N)
     W = rng.integers(-128, 128, size=(M, K), dtype=np.int8)
     Xt = rng.integers(-128, 128, size=(N, K), dtype=np.int8)

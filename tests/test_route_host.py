@@ -1,12 +1,16 @@
-"""us_spmm_route: the kernel a us_spmm call launches (host only; 256 compute units when no GPU is visible)."""
+"""us_spmm_route, us_gemm_i8_route: what a call launches (host only; 256 compute units when no GPU is visible)."""
 import argparse
 import ctypes
+import os
+import re
 import time
 
 import pytest
 
 import bench
-from paper_2608_09291_amd import binding, synth
+import test_gpu_gemm
+import test_gpu_tile
+from paper_2608_09291_amd import binding, build, synth
 
 FORMS = [(4, False), (4, True), (2, False)]
 
@@ -69,6 +73,42 @@ def test_bench_reports_the_kernel_it_times(workload, N, kernel):
     r = binding.spmm_route(w.M, w.K, N)
     assert out["kernel"] == kernel and out["split_k"] == r["split_k"] and out["chunk_lts"] == r["chunk_lts"]
     assert (out["staging"] == "tile") == (kernel == "us_spmm_tile_kernel")
+
+
+def built(header, macro, fields):
+    """The configurations a header lists, cut to `fields` of their columns."""
+    text = open(os.path.join(build.CSRC, header)).read()
+    body = re.search(r"#define " + macro + r"\(X\)(.*?)\n\n", text, re.S).group(1)
+    return [tuple(int(row.split(",")[k]) for k in fields) for row in re.findall(r"X\(([^)]*)\)", body)]
+
+
+@pytest.mark.parametrize("form", ["plain", "reordered", "w2"])
+def test_tile_tests_run_every_configuration(form):
+    cfgs = built("us_spmm_tile.h", "US_TILE_CFGS", range(4))
+    assert len(set(cfgs)) == len(cfgs) == 17
+    for M, K, N, cfg in test_gpu_tile.SHAPES:
+        assert test_gpu_tile.tile_config(M, K, N, form) == cfg, (M, K, N)
+    assert {s[3] for s in test_gpu_tile.SHAPES} == set(cfgs)
+    # The long-slice cases: more than 64 chunks of four LTs, and a last chunk that is empty for one slice.
+    for M, K, N in ((8208, 16704, 1000), (4112, 66304, 500)):
+        assert -(-(K // 64 // test_gpu_tile.tile_config(M, K, N, form)[3]) // 4) > 64
+    assert test_gpu_tile.tile_config(15408, 8256, 200, form) == (4, 4, 2, 2)
+
+
+def test_gemm_tests_run_every_configuration():
+    cfgs = built("us_gemm.h", "US_GEMM_CFGS", range(5))
+    assert len(set(cfgs)) == len(cfgs) == 13
+    for M, K, N, cfg in test_gpu_gemm.SHAPES:
+        assert tuple(binding.gemm_i8_route(M, K, N).values()) == cfg, (M, K, N)
+    assert {s[3] for s in test_gpu_gemm.SHAPES} == set(cfgs)
+
+
+def test_gemm_argument_errors():
+    L, out = binding.lib(), ctypes.byref(binding.GemmRouteInfo())
+    assert L.us_gemm_i8_route(32, 128, 8, None) == -1
+    for M, K, N in ((40, 128, 8), (32, 96, 8), (32, 128, 0), (32, 128, 1025), (0, 64, 1), (16, 130048 + 64, 1)):
+        assert L.us_gemm_i8_route(M, K, N, out) == -2
+    assert L.us_gemm_i8_route(16, 130048, 1024, out) == 0
 
 
 def test_narrow_calls_search_for_a_plan_once():

@@ -45,7 +45,7 @@ def test_registers_fit_and_nothing_spills(texts):
             assert vgpr <= (512 // lw) // 8 * 8, (m.group(1), vgpr, lw)
             assert scratch == 0, m.group(1)
             n += 1
-    assert n >= 3 * 14 + 13, n
+    assert n == 3 * 17 + 13, n
 
 
 def test_m0_is_only_the_direct_loads(texts):
