@@ -266,14 +266,18 @@ hipError_t launch_gemm(const int8_t *w, const int8_t *x, int32_t *y, int M, int 
     return hipGetLastError();
 }
 
+constexpr float kNoLaunch = 3e38f;
+
 // Cost of a configuration in us: generations of the workgroups that the CUs
 // hold, each a start s, per chunk the larger of one wavefront's latency a and
 // the busiest SIMD's share b v (v wavefronts on it), blended a little, and
-// e v for the combine and the stores. (Always inlined: every call has a
-// constant configuration, which leaves two of its ten divisions.)
+// e v for the combine and the stores. A grid of 2^32 threads or more cannot be
+// launched. (Always inlined: every call has a constant configuration, which
+// leaves two of its ten divisions.)
 __attribute__((always_inline)) inline float gemm_cost(const GemmCfg &c, int64_t nrb, int nkb, int N, int n_cu) {
     const int w = c.WM * c.WN * c.WK, lds = c.WK * c.NB * 128 * 16 * (c.R * c.WM + c.C * c.WN);
     const int64_t groups = (nrb + c.R * c.WM - 1) / (c.R * c.WM), cols = 16 * c.C * c.WN, tiles = (N + cols - 1) / cols;
+    if ((groups + 7) / 8 * tiles >= ((int64_t)1 << 23) / w) return kNoLaunch;
     const int by_lds = kMaxLds / lds, by_regs = 4 * c.LW / w > 0 ? 4 * c.LW / w : 1;
     int per_cu = by_lds < by_regs ? by_lds : by_regs;
     if (per_cu > 16) per_cu = 16;
@@ -318,7 +322,8 @@ static_assert(kGemmCfgs[2].R == 1 && kGemmCfgs[2].WK == 4 && kGemmCfgs[3].R == 2
 
 // The configuration with the lowest cost. Wide tiles are left out where more
 // than half of their columns would be empty; the first configuration takes
-// every shape.
+// every shape, up to the rows of one grid (2^30 / column tiles), and the last
+// one, with the fewest workgroups, what then is left.
 template <int... I>
 inline int gemm_pick(int64_t nrb, int nkb, int N, int n_cu, std::integer_sequence<int, I...>) {
     int best = -1;
@@ -334,6 +339,7 @@ inline int gemm_pick(int64_t nrb, int nkb, int N, int n_cu, std::integer_sequenc
         }
     };
     (consider(std::integral_constant<int, I>()), ...);
+    if (cost >= kNoLaunch) return (int)sizeof...(I) - 1;
     return N <= 8 ? gemm_narrow(best, nrb, nkb, n_cu) : best;
 }
 

@@ -2,6 +2,7 @@
 import argparse
 import ctypes
 import os
+import random
 import re
 import time
 
@@ -116,6 +117,23 @@ def test_gemm_tests_run_every_configuration():
 def test_gemm_choice_of_large_narrow_products(M, K, N, row_blocks, split_k):
     r = binding.gemm_i8_route(M, K, N)
     assert (r["row_blocks"], r["split_k"]) == (row_blocks, split_k)
+
+
+def test_gemm_grids_can_be_launched():
+    # A grid holds fewer than 2^32 threads. Every product that fits 288 GB of
+    # HBM, for M below 2^30, as with one row block per 64 threads.
+    rng = random.Random(1)
+    shapes = [(1 << 28, 64, 49), (1 << 29, 64, 17), ((1 << 30) - 16, 64, 1), (1 << 27, 256, 32)]
+    while len(shapes) < 20000:
+        M, K, N = (int(2 ** rng.uniform(a, b)) for a, b in ((14, 26), (0, 11), (0, 10)))
+        M, K = 16 * M, 64 * K
+        if K <= 130048 and M * K + 4 * M * N + K * N <= 288e9:
+            shapes.append((M, K, N))
+    for M, K, N in shapes:
+        r = binding.gemm_i8_route(M, K, N)
+        groups, tiles = -(-M // (16 * r["row_blocks"] * r["waves_m"])), -(-N // (16 * r["col_blocks"] * r["waves_n"]))
+        threads = 64 * r["waves_m"] * r["waves_n"] * r["split_k"]
+        assert 8 * -(-groups // 8) * tiles * threads < 1 << 32, (M, K, N, r)
 
 
 def test_gemm_argument_errors():
