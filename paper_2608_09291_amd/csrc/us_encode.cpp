@@ -258,11 +258,31 @@ us_status encode_impl(const int8_t *w, int32_t M, int32_t K, int64_t ldw, bool r
     // Pass 1: check that every weight is a signed `bits`-bit value; row
     // reordering (optional), then the shared union mask B_t and P_t =
     // ||B_t||_0 per LT; count nonzeros. One pass over W: a row's nonzero mask
-    // gives its count, its folded mask (Eq. 3) and its part of B_t.
+    // gives its count, its folded mask (Eq. 3) and its part of B_t. Every
+    // thread stops at the first weight out of range. Reordering takes a
+    // hundred times as long as the check, which therefore runs ahead of it.
     const int lo = -(1 << (bits - 1)), hi = (1 << (bits - 1)) - 1;
     std::atomic<int64_t> nnz{0};
     std::atomic<bool> bad{false}, oom{false};
-    parallel_ranges(n_lt, [&](int64_t t0, int64_t t1) {
+    // Folded masks of LT t's rows; true if all of its weights are in range.
+    auto fold_rows = [&](int64_t t, uint32_t fold[US_LT_H], int64_t &count) {
+        const int8_t *base = w + (t / nkb) * US_LT_H * ldw + (t % nkb) * US_LT_W;
+        bool out_of_range = false;
+        for (int r = 0; r < US_LT_H; ++r) {
+            const uint64_t m = row_mask(base + (int64_t)r * ldw, lo, hi, out_of_range);
+            count += popcount64(m);
+            fold[r] = (uint32_t)m | (uint32_t)(m >> kAreaW);
+        }
+        if (out_of_range) bad.store(true, std::memory_order_relaxed);
+        return !out_of_range;
+    };
+    if (reorder)
+        parallel_ranges(n_lt, [&](int64_t t0, int64_t t1) {
+            uint32_t fold[US_LT_H];
+            int64_t count = 0;
+            for (int64_t t = t0; t < t1 && !bad.load(std::memory_order_relaxed); ++t) fold_rows(t, fold, count);
+        });
+    if (!bad) parallel_ranges(n_lt, [&](int64_t t0, int64_t t1) {
         RowPairing *dp = nullptr;
         if (reorder) {
             try {
@@ -273,16 +293,9 @@ us_status encode_impl(const int8_t *w, int32_t M, int32_t K, int64_t ldw, bool r
             }
         }
         int64_t local_nnz = 0;
-        bool local_bad = false;
-        for (int64_t t = t0; t < t1; ++t) {
-            const int8_t *base = w + (t / nkb) * US_LT_H * ldw + (t % nkb) * US_LT_W;
+        for (int64_t t = t0; t < t1 && !bad.load(std::memory_order_relaxed); ++t) {
             uint32_t fold[US_LT_H];
-            for (int r = 0; r < US_LT_H; ++r) {
-                const uint64_t m = row_mask(base + (int64_t)r * ldw, lo, hi, local_bad);
-                local_nnz += popcount64(m);
-                fold[r] = (uint32_t)m | (uint32_t)(m >> kAreaW);
-            }
-            if (local_bad) break;
+            if (!fold_rows(t, fold, local_nnz)) break;
             uint8_t pi[US_LT_H];
             for (int p = 0; p < US_LT_H; ++p) pi[p] = (uint8_t)p;
             if (dp) {
@@ -301,7 +314,6 @@ us_status encode_impl(const int8_t *w, int32_t M, int32_t K, int64_t ldw, bool r
             P[(size_t)t] = p;
         }
         delete dp;
-        if (local_bad) bad = true;
         nnz += local_nnz;
     });
     if (bad || oom) {
