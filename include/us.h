@@ -46,9 +46,9 @@ typedef enum {
 #define US_WORDS_PER_LT 4   /* 8 x 32 union-mask bits = four 64-bit words  */
 #define US_PAYLOAD_PAD 16   /* zero bytes after the payload                */
 #define US_N_MAX 32         /* widest activation matrix of one kernel pass */
-#define US_N_LIMIT 1024     /* widest activation matrix; with a forced
-                               configuration N > US_N_MAX runs as slabs of
-                               US_N_MAX columns, each streaming W */
+#define US_N_LIMIT 1024     /* widest activation matrix; where us_spmm does not
+                               take the tile kernel, N > US_N_MAX runs as slabs
+                               of US_N_MAX columns, each streaming W */
 #define US_K_MAX 130048     /* K bound: int32 headroom of the kernel's scaled sums */
 
 /*
@@ -321,9 +321,10 @@ us_status us_spmm_workspace_size(int32_t M, int32_t K, int32_t N, const us_spmm_
  *            w->bits = 2 multiplies a W2A4 matrix
  *   x      : device, N x K row-major INT4, two values per byte along K
  *            (even k in the low nibble), 16-byte aligned
- *   N      : 1..US_N_LIMIT activation columns, in one launch; with a
- *            forced configuration, beyond US_N_MAX (32), one pass per slab
- *            of 32 columns (the last one narrower), each with its own
+ *   N      : 1..US_N_LIMIT activation columns, in one launch. With a
+ *            forced configuration, for more than 2^22 rows, and at K = 64 up
+ *            to 48 columns: beyond US_N_MAX (32) one pass per slab of 32
+ *            columns (the last one narrower), each with its own
  *            configuration and each reading W again
  *   y      : device int32, N x M row-major (y[n * M + m] = Y[m][n])
  *   scale  : device float32[M] or NULL; with it, y_f32[n * M + m] =

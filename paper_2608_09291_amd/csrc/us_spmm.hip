@@ -1,7 +1,8 @@
 // Host side of the IE-BME SpMM (Section VI, "UnionSparse Kernel"
 // algorithm): argument checks, the choice of kernel family, split and chunk
-// configuration, and the launch. The kernels are in us_spmm_kernel.h
-// (chunked) and us_spmm_burst.h (single pass).
+// configuration, and the launch. The kernels are in us_spmm_tile.h (most
+// automatic calls), us_spmm_kernel.h (chunked) and us_spmm_burst.h (single
+// pass).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

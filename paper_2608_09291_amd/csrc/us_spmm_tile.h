@@ -1,7 +1,8 @@
 // IE-BME x INT4 -> INT32 sparse product on gfx950: the tile kernel, which
-// automatic calls of every width take. Same operation and format as the chunked kernel
-// of us_spmm_kernel.h (Section VI: the UnionSparse kernel, its LSPD decode
-// and split-K); what differs:
+// automatic calls of every width take, except some narrow ones (use_tile), up
+// to 48 columns at K = 64, and matrices of more than 2^22 rows. Same operation
+// and format as the chunked kernel of us_spmm_kernel.h (Section VI: the
+// UnionSparse kernel, its LSPD decode and split-K); what differs:
 //
 //  * Wavefront tile. A wavefront multiplies R row blocks by C column blocks of
 //    16, so that an expanded activation operand feeds R matrix instructions
@@ -90,7 +91,7 @@ struct TileCfg {
 constexpr TileCfg kTileCfgs[] = {US_TILE_CFGS(US_TILE_ROW)};
 #undef US_TILE_ROW
 constexpr int kNumTileCfgs = sizeof(kTileCfgs) / sizeof(kTileCfgs[0]);
-constexpr int kTileMaxM = 1 << 22;   // 128 columns of Y stay within a 32-bit offset
+constexpr int kTileMaxM = 1 << 22;   // 128 columns of Y stay within 2^31 bytes
 
 struct TileArgs {
     SpmmArgs a;
@@ -422,15 +423,16 @@ __global__ __launch_bounds__(64 * WM * WK, PERM && LW == 8 ? 7 : LW) void us_spm
 
     // Stores through buffers over this tile's columns of Y and Yf: columns
     // past N lie outside them and are dropped. (At most 128 columns of 4 M
-    // bytes: the host takes this path for M < 2^22.)
+    // bytes, 2^31 in all: the host takes this path for M <= 2^22. Sizes and
+    // offsets of buffers are unsigned.)
     constexpr int kShift = BITS == 4 ? 8 : 10;
     constexpr int kBlocks = R * C;
     const uint32_t row4 = 4u * (uint32_t)m_;                  // bytes of one column of Y
-    const int tile_bytes = (int)(row4 * (uint32_t)min(16 * C, N - n0));
+    const uint32_t tile_bytes = row4 * (uint32_t)min(16 * C, N - n0);
     const __amdgpu_buffer_rsrc_t ydst =
-        __builtin_amdgcn_make_buffer_rsrc((void *)(y + (int64_t)n0 * m_), (short)0, tile_bytes, kBufferDword3);
+        __builtin_amdgcn_make_buffer_rsrc((void *)(y + (int64_t)n0 * m_), (short)0, (int)tile_bytes, kBufferDword3);
     const __amdgpu_buffer_rsrc_t fdst = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(yf + (scale ? (int64_t)n0 * m_ : 0)), (short)0, scale ? tile_bytes : 0, kBufferDword3);
+        (void *)(yf + (scale ? (int64_t)n0 * m_ : 0)), (short)0, scale ? (int)tile_bytes : 0, kBufferDword3);
     // Lane (rr, g), element v: row 8 (rr & 1) + rr / 2 of its row block, column 4 g + v.
     const uint32_t lane_off = 4u * m_in + (uint32_t)(4 * g) * row4;
     if constexpr (WK == 1) {

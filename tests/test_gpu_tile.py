@@ -108,3 +108,23 @@ def test_long_slices(torch_cuda, M, K, N, form):
     binding.spmm(dev, xp, N, y0, variant=1)
     torch.cuda.synchronize()
     assert torch.equal(y, y0)
+
+
+def test_most_rows(torch_cuda):
+    """The most rows the tile kernel takes: a column tile of Y is 2^31 bytes.
+    The matrix repeats 4096 rows, and so do the columns of Y."""
+    torch = torch_cuda
+    M, K, N, rep = 1 << 22, 64, 150, 4096
+    announce(f"tile M={M} K={K} N={N}")
+    assert tile_config(M, K, N, "plain") and not tile_config(M + 16, K, N, "plain")
+    W, Xt, sc = synth.random_problem(rep, K, N, 0.5, 13)
+    dev = binding.to_device(binding.encode(np.tile(W, (M // rep, 1))))
+    xp, scale = torch.from_numpy(binding.pack_int4(Xt)).cuda(), torch.from_numpy(np.tile(sc, M // rep)).cuda()
+    y = torch.full((N, M), -1, dtype=torch.int32, device="cuda")
+    yf = torch.full((N, M), float("nan"), dtype=torch.float32, device="cuda")
+    binding.spmm(dev, xp, N, y, scale, yf)
+    torch.cuda.synchronize()
+    check(y[:, :rep].cpu().numpy().T, yf[:, :rep].cpu().numpy().T, W, Xt, sc)
+    for v in (y, yf):
+        v = v.view(N, M // rep, rep)
+        assert bool((v == v[:, :1]).all())

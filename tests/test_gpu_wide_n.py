@@ -1,9 +1,10 @@
-"""GPU parity for activation widths beyond one kernel pass (N > 32, prefill sizes).
+"""GPU parity for activation widths beyond 32 columns (prefill sizes).
 
-us_spmm and us_gemm_i8 run such N as slabs of 32 columns, each slab with its
-own launch configuration and its own offsets into X, Y and the dequantised
-Y. Y must equal the oracle's int64 product for every column, including the
-ragged last slab.
+Automatic us_spmm calls and us_gemm_i8 run such N in one launch of column
+tiles; a forced configuration (and K = 64 up to 48 columns) runs slabs of 32
+columns, each with its own launch configuration and its own offsets into X, Y
+and the dequantised Y. Y must equal the oracle's int64 product for every
+column, including a ragged last tile or slab.
 """
 import numpy as np
 import pytest
@@ -16,11 +17,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,K,N,s,seed", [
-    (32, 640, 33, 0.5, 1),       # one full slab and a 1-column slab
+    (32, 640, 33, 0.5, 1),       # one column beyond a block of 16
     (48, 1280, 48, 0.3, 2),
-    (64, 1024, 64, 0.5, 3),      # two full slabs
+    (64, 1024, 64, 0.5, 3),      # whole column blocks
     (16, 2496, 65, 0.7, 4),
-    (128, 768, 100, 0.5, 5),     # 32 + 32 + 32 + 4
+    (128, 768, 100, 0.5, 5),     # a last block of 4
     (64, 4096, 128, 0.6, 6),
     (32, 512, 256, 0.5, 7),
     (16, 128, 1024, 0.5, 8),     # the widest accepted
@@ -28,6 +29,16 @@ pytestmark = pytest.mark.gpu
 def test_wide_n_parity(torch_cuda, M, K, N, s, seed):
     announce(f"wide N M={M} K={K} N={N} s={s}")
     W, Xt, sc = synth.random_problem(M, K, N, s, seed)
+    Y, Yf = run_spmm(torch_cuda, W, Xt, sc)
+    check(Y, Yf, W, Xt, sc)
+
+
+@pytest.mark.parametrize("N,launches", [(33, 2), (48, 2), (49, 1)])
+def test_wide_n_one_lt(torch_cuda, N, launches):
+    """A K of one LT: slabs up to 48 columns, the tile kernel above."""
+    announce(f"wide N K=64 N={N}")
+    assert binding.spmm_route(208, 64, N)["launches"] == launches
+    W, Xt, sc = synth.random_problem(208, 64, N, 0.5, N)
     Y, Yf = run_spmm(torch_cuda, W, Xt, sc)
     check(Y, Yf, W, Xt, sc)
 
