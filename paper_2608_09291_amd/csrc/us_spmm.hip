@@ -217,13 +217,29 @@ us_status make_plan(int M, int K, int N, bool perm, int bits, const us_spmm_opts
 //    50 % sparsity, 6.58 against 6.85 at 30 %;
 //  - 16 wavefronts of 8-LT chunks up to 8 columns: 2048x8192 N = 4 4.87
 //    against 5.05 us.
-// At 12 columns on rows in stored order all of these lose by 9 % or more.
-bool use_tile(const Plan &chunked, int K, int N, bool perm, int bits) {
-    const int nkb = K / US_LT_W, ch = kCfgs[chunked.cfg].ch;
-    if (chunked.gens != 1 || (nkb + chunked.wpg - 1) / chunked.wpg > ch) return true;
-    if (ch == 11) return !(N <= 8 || perm || bits == 2);
-    if (ch == 16) return N > 4;
-    return !(ch == 8 && chunked.wpg == 16 && N <= 8);
+// and, on 4-bit rows in stored order, where the tile kernel's choice `t` gains
+// little from its own split:
+//  - linear 11-LT chunks at 9 to 16 columns where it splits K no further, with
+//    a row block for every second CU: 7536x2496 N = 16 4.72 against 5.34 us,
+//    4560x2560 N = 12 4.37 against 4.86, 3296x4800 N = 12 4 % (with more
+//    slices than the chunked kernel it is 8-15 % the faster);
+//  - 4 wavefronts of slices of up to 6 LTs at up to 4 columns, which it halves:
+//    10832x1536 N = 4 4.20 against 4.45, 4656x1472 N = 4 3.57 against 3.70;
+//  - 8-LT chunks at up to 4 columns against its two row blocks per wavefront:
+//    23184x896 N = 3 4.75 against 5.05 us.
+// Other calls of these widths lose on the chunked kernel: ring stages at 12
+// columns 2-9 %, 16-LT chunks above 4 columns 8 %.
+bool use_tile(const Plan &chunked, const TileCfg &t, int nrb, int nkb, int N, bool perm, int bits, int n_cu) {
+    const ChunkCfg &c = kCfgs[chunked.cfg];
+    const int slice = (nkb + chunked.wpg - 1) / chunked.wpg;
+    const bool plain = !perm && bits == 4;
+    if (chunked.gens != 1 || slice > c.ch) return true;
+    if (c.ch == 11)
+        return plain && N > 8 && (c.ring || t.WK != chunked.wpg || 2 * nrb < n_cu);
+    if (c.ch == 16) return N > 4;
+    if (c.ch != 8) return true;
+    if (chunked.wpg == 16) return N > 8;
+    return !(plain && N <= 4 && (t.R > 1 || (chunked.wpg == 4 && slice <= 6)));
 }
 
 // What a call launches: the tile kernel in configuration `tile`, or (tile < 0)
@@ -252,9 +268,12 @@ us_status plan_call(int M, int K, int N, bool perm, int bits, const us_spmm_opts
         if (c.tile >= 0) return US_OK;
     }
     if ((st = make_plan(M, K, c.n_full, perm, bits, opts, n_cu, ws_ok, c.full)) != US_OK) return st;
-    if (may_tile && N <= 16 && use_tile(c.full, K, N, perm, bits)) {
-        c.tile = tile_pick(M / US_LT_H, K / US_LT_W, N, bits, n_cu);
-        if (c.tile >= 0) return US_OK;
+    if (may_tile && N <= 16) {
+        const int nrb = M / US_LT_H, nkb = K / US_LT_W, tile = tile_pick(nrb, nkb, N, bits, n_cu);
+        if (tile >= 0 && use_tile(c.full, kTileCfgs[tile], nrb, nkb, N, perm, bits, n_cu)) {
+            c.tile = tile;
+            return US_OK;
+        }
     }
     c.last = c.full;
     return c.n_last == c.n_full ? US_OK : make_plan(M, K, c.n_last, perm, bits, opts, n_cu, ws_ok, c.last);

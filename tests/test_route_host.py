@@ -21,6 +21,18 @@ FORMS = [(4, False), (4, True), (2, False)]
     (28672, 8192, 1, "us_spmm_tile_kernel", 1),
     (28672, 8192, 32, "us_spmm_tile_kernel", 1),
     (12288, 4096, 1024, "us_spmm_tile_kernel", 1),
+    # Narrow calls that the tile kernel splits no further, or hardly, than the chunked one does ...
+    (7536, 2496, 16, "us_spmm_kernel", 1),
+    (5120, 2432, 11, "us_spmm_kernel", 1),
+    (3296, 4800, 12, "us_spmm_kernel", 1),
+    (10832, 1536, 4, "us_spmm_kernel", 1),
+    (23184, 896, 3, "us_spmm_kernel", 1),
+    # ... and some that it does, or with fewer row blocks, or wider
+    (5040, 1216, 12, "us_spmm_tile_kernel", 1),
+    (880, 4992, 15, "us_spmm_tile_kernel", 1),
+    (10832, 1536, 5, "us_spmm_tile_kernel", 1),
+    (26640, 768, 3, "us_spmm_tile_kernel", 1),
+    (4096, 11008, 12, "us_spmm_tile_kernel", 1),
     (4096, 64, 40, "us_spmm_kernel", 2),               # one LT per row block: no tile of that width
     (4096, 64, 49, "us_spmm_tile_kernel", 1),
     ((1 << 22) + 16, 64, 1024, "us_spmm_kernel", 32),  # Y beyond the tile kernel's offsets
