@@ -38,7 +38,7 @@ HBM_PEAK_GBS = 8000.0
 ROTATE_BYTES = 1 << 30
 ROUND_LAUNCHES = 200
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2608_09291_amd", "csrc", f)
-               for f in ("us_spmm_kernel.h", "us_range.h", "us_spmm.hip", "us_spmm_narrow.hip", "us_spmm_perm.hip",
+               for f in ("us_spmm_kernel.h", "us_range.h", "us_device.h", "us_spmm.hip", "us_spmm_narrow.hip", "us_spmm_perm.hip",
                          "us_spmm_w2.hip", "us_spmm_wide.hip", "us_spmm_wide8.hip", "us_spmm_burst.h", "us_spmm_burst_plain.hip",
                          "us_spmm_burst_narrow.hip", "us_spmm_burst_perm.hip", "us_spmm_burst_w2.hip", "us_spmm_tile.h",
                          "us_spmm_tile_plain.hip", "us_spmm_tile_perm.hip", "us_spmm_tile_w2.hip")] + [
@@ -57,7 +57,7 @@ KERNEL_SRCS = [os.path.join(ROOT, "paper_2608_09291_amd", "csrc", f)
 # traffic is unknown. Keyed by workload, N and row reordering.
 COPY_FACTOR = {"FETCH_SIZE": 131083.0 / 262144.0, "WRITE_SIZE": 262144.0 / 262144.0}
 MEASURED_TRAFFIC = {
-    ("ffn_down_4096x11008_s50", 8, False): dict(src="bc69ae965d9e8968", FETCH_SIZE=11374.3125, WRITE_SIZE=256.0),
+    ("ffn_down_4096x11008_s50", 8, False): dict(src="10eb1c459e9f0345", FETCH_SIZE=11374.75, WRITE_SIZE=256.0),
 }
 
 

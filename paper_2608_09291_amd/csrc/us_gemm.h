@@ -9,17 +9,19 @@
 //
 // What bounds it is getting operands into a CU: HBM at few columns (W is read
 // once), L2 at many (every workgroup reads its rows and columns). So operands
-// go straight into LDS in whole 128-byte lines, 8 rows per load (98 B/ns per
-// CU from L2 against 37 for the matrix layout's 16 rows x 64 bytes loaded
-// into registers, as measured), the tile grows with the problem, and all
-// columns are one launch instead of one pass over W per 32 columns.
+// go straight into LDS in whole 128-byte lines, 8 rows per load (118 B/ns per
+// CU from L2 against 38 for the matrix layout's 16 rows x 64 bytes, as
+// measured), the tile grows with the problem, and all columns are one launch
+// instead of one pass over W per 32 columns.
 //
-// us per call, that kernel -> this one (weights rotating over three copies):
-// 4096x11008 N = 8 14.3 -> 9.2, N = 32 24 -> 12, N = 256 196 -> 22;
-// 12288x4096 N = 512 332 -> 33; 8192x8192 N = 1024 897 -> 65. Over 341 swept
-// shapes (M 256-16384, K 256-11008) the choice of gemm_pick takes 0.71 of the
-// time at N = 1-16, 0.50 at 17-32, 0.23 at 33-128 and 0.08 above (geometric
-// means; worst case 1.03). Non-temporal weight loads were up to 20 % slower.
+// us per call, the register kernel before it -> this one, weights rotating past
+// the 256 MB cache: 4096x11008 N = 8 15.1 -> 10.5, N = 32 24.9 -> 14.8, N = 256
+// 195 -> 29; 12288x4096 N = 512 333 -> 45; 8192x8192 N = 1024 900 -> 78. Over
+// three copies of the weights, which that cache holds, 4096x11008 takes 9.0 at
+// N = 8 and 22.3 at N = 256. Over 60 drawn shapes (M, K 256-16384) the choice
+// of gemm_pick takes 0.79 of the time at N = 1-16, 0.61 at 17-32, 0.29 at
+// 33-128 and 0.13 above (geometric means; the slowest, a call of 2 us, 0.4 us
+// more). Non-temporal weight loads were up to 20 % slower.
 #ifndef UNIONSPARSE_US_GEMM_H
 #define UNIONSPARSE_US_GEMM_H
 

@@ -205,8 +205,8 @@ us_status make_plan(int M, int K, int N, bool perm, int bits, const us_spmm_opts
 
 // Whether an automatic call takes the tile kernel (us_spmm_tile.h), which
 // runs all columns in one launch. It was the faster on nearly every shape
-// swept, on average by 4x above 32 columns, 1.27x at 17-32 and 1.13x up to 16
-// (by up to 1.4x there). The chunked kernel keeps narrow calls that it runs
+// swept, on average by 4x above 32 columns, 1.2x at 17-32 and 1.09x up to 16
+// (by up to 1.6x there). The chunked kernel keeps narrow calls that it runs
 // in one generation of workgroups with one chunk per wavefront where that
 // chunk fits the slice and the tile kernel's chunks of four LTs do not:
 //  - 11-LT chunks (slices of 9 to 11 LTs, three chunks of the tile kernel) up

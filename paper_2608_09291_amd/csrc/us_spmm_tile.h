@@ -8,10 +8,11 @@
 //    16, so that an expanded activation operand feeds R matrix instructions
 //    and a decoded weight operand C of them. The chunked kernel decodes W and
 //    expands X once per 16 x 32 outputs, and reads W again for every 32
-//    columns; here all columns are one launch. The cost of both expansions is
-//    what bounds wide N: on gfx950 a SIMD was measured to take
-//    max(16, 8 + 4 v) cycles per v_mfma_i32_16x16x64_i8 with v other vector
-//    instructions beside it.
+//    columns; here all columns are one launch. Both expansions compete with
+//    the matrix instructions for issue: a SIMD with four wavefronts was
+//    measured to take 7.5 ns per v_mfma_i32_16x16x64_i8 with up to two other
+//    vector instructions beside it, 9.3 with three, 12.0 with four, 14.4 with
+//    six, 16.4 with eight, and 1 ns for each further one.
 //
 //  * Lane groups take LTs, not segments. A chunk is four LTs of a row block.
 //    Lane (rr, g) owns mask row i = rr / 2, area row rr % 2 of LT g, and
@@ -23,8 +24,8 @@
 //    read with two 16-byte LDS reads and no transposition.
 //
 //  * Activations go straight into LDS, 8 columns x 128 bytes per load, lanes
-//    along the row: 16 rows x 64 bytes per load was measured at 37 B/ns per
-//    CU from L2, 8 x 128 at 98, contiguous bytes at 117. The 16-byte pieces
+//    along the row: 16 rows x 64 bytes per load was measured at 38 B/ns per
+//    CU from L2, 8 x 128 at 118, contiguous bytes at 133. The 16-byte pieces
 //    are placed with an XOR so that the reads of 16 columns fall in different
 //    banks. With WM > 1 the WM wavefronts of a K slice stack along M and
 //    share two such stages (one barrier per chunk); with WM = 1 every
@@ -37,13 +38,15 @@
 //    64 chunks are worked out at once, one chunk per lane, so that a request
 //    is a few scalar instructions.
 //
-// Measured against the chunked kernel (us per call, weights 50 % sparse where
-// not said, before -> after): 12288x4096 N = 1024 300 -> 57, 4096x11008
-// N = 256 82 -> 25, N = 100 37 -> 16, 28672x8192 70 % sparse N = 32 37 -> 24,
-// 13824x5120 60 % N = 16 11.2 -> 8.9, 28672x8192 70 % N = 1 20.8 -> 17.8,
-// 11008x4096 N = 8 6.8 -> 6.0, 1024x4096 N = 8 4.1 -> 3.5. Geometric means
-// over 1256 swept shapes (M 256-28672, K 512-28672) with the choice of
-// tile_pick: 0.25 of the time at N = 33-1024, 0.79 at 17-32, 0.88 at 1-16.
+// Measured against the chunked kernel (us per call, launched back to back on
+// weights that rotate past the 256 MB cache, 50 % sparse where not said,
+// before -> after): 12288x4096 N = 1024 301 -> 59, 4096x11008 N = 256 81 -> 26,
+// N = 100 37 -> 16, 28672x8192 70 % sparse N = 32 35 -> 24, 13824x5120 60 %
+// N = 16 11.9 -> 9.3, 28672x8192 70 % N = 1 21.2 -> 19.2 and reordered N = 5
+// 25.2 -> 20.3, 11008x4096 N = 8 7.0 -> 6.7, 1024x4096 N = 8 4.1 -> 3.6.
+// Geometric means over 330 drawn shapes (M 256-28672, K 256-28672, every
+// weight form) with the choice of tile_pick: 0.24 of the time at N = 33-1024,
+// 0.83 at 17-32, 0.92 at 1-16.
 #ifndef UNIONSPARSE_US_SPMM_TILE_H
 #define UNIONSPARSE_US_SPMM_TILE_H
 
