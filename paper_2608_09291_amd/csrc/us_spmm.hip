@@ -203,6 +203,22 @@ us_status make_plan(int M, int K, int N, bool perm, int bits, const us_spmm_opts
     return pl.cfg < 0 ? US_ERR_ARG : US_OK;               // no configuration fits LDS
 }
 
+// Many row blocks of few LTs: a wavefront of the chunked kernel takes a whole
+// row block, or half of one, while the tile kernel's chunks of four LTs are
+// split over two wavefronts or more and mostly empty. us per call, chunked
+// against tile: 1048576x128 N = 1 33.5 / 64.1, N = 32 82.8 / 110.8; 262144x256
+// N = 1 12.5 / 19.3, N = 16 17.3 / 21.8, N = 32 23.9 / 30.5; 49152x256 N = 8 to
+// 32 22-30 % apart; at 32768 rows level. Longer row blocks: 81920x512 N = 1
+// 17 %, 262144x768 N = 1 22 %, 524288x320 N = 8 7 %, 131072x320 N = 32 10 %;
+// at 9 to 16 columns, with 2-bit weights or 16 LTs the tile kernel is ahead.
+bool tall(int nrb, int nkb, int N, int bits, int n_cu) {
+    const int per_cu = nrb / n_cu;
+    if (per_cu < 10 || N > 32) return false;
+    if (nkb <= 4) return true;
+    if (N > 16) return nkb <= 6 && per_cu >= 32;
+    return bits == 4 && per_cu >= 12 && (N <= 4 ? nkb <= 12 : N <= 8 && nkb <= 6);
+}
+
 // Whether an automatic call takes the tile kernel (us_spmm_tile.h), which
 // runs all columns in one launch. It was the faster on nearly every shape
 // swept, on average by 4x above 32 columns, 1.2x at 17-32 and 1.09x up to 16
@@ -233,6 +249,7 @@ bool use_tile(const Plan &chunked, const TileCfg &t, int nrb, int nkb, int N, bo
     const ChunkCfg &c = kCfgs[chunked.cfg];
     const int slice = (nkb + chunked.wpg - 1) / chunked.wpg;
     const bool plain = !perm && bits == 4;
+    if (tall(nrb, nkb, N, bits, n_cu)) return false;
     if (chunked.gens != 1 || slice > c.ch) return true;
     if (c.ch == 11)
         return plain && N > 8 && (c.ring || t.WK != chunked.wpg || 2 * nrb < n_cu);
@@ -263,13 +280,14 @@ us_status plan_call(int M, int K, int N, bool perm, int bits, const us_spmm_opts
     // The search for a chunked plan is the host's largest share of a narrow
     // call (about 0.5 us; the tile kernel's 0.04), so each plan is made once:
     // that of up to 16 columns, which the route needs, serves the launch too.
-    if (may_tile && N > 16) {
-        c.tile = tile_pick(M / US_LT_H, K / US_LT_W, N, bits, n_cu);
+    const int nrb = M / US_LT_H, nkb = K / US_LT_W;
+    if (may_tile && N > 16 && !tall(nrb, nkb, N, bits, n_cu)) {
+        c.tile = tile_pick(nrb, nkb, N, bits, n_cu);
         if (c.tile >= 0) return US_OK;
     }
     if ((st = make_plan(M, K, c.n_full, perm, bits, opts, n_cu, ws_ok, c.full)) != US_OK) return st;
     if (may_tile && N <= 16) {
-        const int nrb = M / US_LT_H, nkb = K / US_LT_W, tile = tile_pick(nrb, nkb, N, bits, n_cu);
+        const int tile = tile_pick(nrb, nkb, N, bits, n_cu);
         if (tile >= 0 && use_tile(c.full, kTileCfgs[tile], nrb, nkb, N, perm, bits, n_cu)) {
             c.tile = tile;
             return US_OK;

@@ -1,8 +1,9 @@
 // IE-BME x INT4 -> INT32 sparse product on gfx950: the tile kernel, which
-// automatic calls of every width take, except some narrow ones (use_tile), up
-// to 48 columns at K = 64, and matrices of more than 2^22 rows. Same operation
-// and format as the chunked kernel of us_spmm_kernel.h (Section VI: the
-// UnionSparse kernel, its LSPD decode and split-K); what differs:
+// automatic calls of every width take, except some of up to 32 columns
+// (use_tile, tall), up to 48 columns at K = 64, and matrices of more than 2^22
+// rows. Same operation and format as the chunked kernel of us_spmm_kernel.h
+// (Section VI: the UnionSparse kernel, its LSPD decode and split-K); what
+// differs:
 //
 //  * Wavefront tile. A wavefront multiplies R row blocks by C column blocks of
 //    16, so that an expanded activation operand feeds R matrix instructions

@@ -33,6 +33,16 @@ FORMS = [(4, False), (4, True), (2, False)]
     (10832, 1536, 5, "us_spmm_tile_kernel", 1),
     (26640, 768, 3, "us_spmm_tile_kernel", 1),
     (4096, 11008, 12, "us_spmm_tile_kernel", 1),
+    # Many row blocks of few LTs, and some that the tile kernel runs faster
+    (1048576, 128, 1, "us_spmm_kernel", 1),
+    (1048576, 128, 32, "us_spmm_kernel", 1),
+    (49152, 256, 16, "us_spmm_kernel", 1),
+    (262144, 768, 1, "us_spmm_kernel", 1),
+    (131072, 320, 32, "us_spmm_kernel", 1),
+    (28672, 256, 16, "us_spmm_tile_kernel", 1),
+    (262144, 320, 16, "us_spmm_tile_kernel", 1),
+    (262144, 768, 24, "us_spmm_tile_kernel", 1),
+    (262144, 256, 100, "us_spmm_tile_kernel", 1),
     (4096, 64, 40, "us_spmm_kernel", 2),               # one LT per row block: no tile of that width
     (4096, 64, 49, "us_spmm_tile_kernel", 1),
     ((1 << 22) + 16, 64, 1024, "us_spmm_kernel", 32),  # Y beyond the tile kernel's offsets
