@@ -299,24 +299,25 @@ __attribute__((always_inline)) inline float gemm_cost(const GemmCfg &c, int64_t 
 // What a large matrix takes at up to 8 columns instead of the configuration of
 // lowest cost. The costs were fitted to M <= 16384 and know no HBM limit. With
 // rows of 1 KB and more they send larger matrices to config 0 (no K slices),
-// which streams W at 4.2-4.8 TB/s where it has at most 7 wavefronts per CU to
-// request it, or rows a multiple of 4 KB apart, against 5.2-6 with four slices;
-// and with rows above 8 KB to four slices, each wavefront's own above 2 KB
-// (4.4 TB/s against 5.5 with eight). us per call at N = 1, that choice -> this
-// one, against the kernel that this file replaced (16 rows x 64 bytes into
-// registers): 28672x1536 10.3 -> 9.2 against 10.1, 28672x4096 26.3 -> 22.5
-// against 23.3, 28672x8192 45.4 -> 41.0 against 49.0, 53248x4096 46.5 -> 40.4
-// against 45.9, 28672x11008 80.9 -> 59.9 against 67.1, 16384x16384 62.4 -> 48.6
-// against 54.5. Config 1 (eight slices) holds two workgroups per CU; where that
-// leaves a second, part-filled generation, four slices (five per CU) are faster
-// up to 8 KB: 12288x8192 20.8 -> 18.0 against 20.2, 8720x8192 17.9 -> 14.0
-// against 19.1. With more wavefronts config 0 stays (49152x2048 17.6 against
-// 18.1), and above 8 columns, where it already was ahead, the lowest cost
-// (53248x4096 N = 16 43.0 against 44.4).
+// which streams W at 4.2-4.8 TB/s where it has fewer than 8 wavefronts per CU
+// to request it, or rows a multiple of 4 KB apart, against 5.2-6 with four
+// slices; and with rows above 8 KB to four slices, each wavefront's own above
+// 2 KB (4.4 TB/s against 5.5 with eight). us per call at N = 1, that choice ->
+// this one, against the kernel that this file replaced (16 rows x 64 bytes
+// into registers): 28672x1536 10.3 -> 9.2 against 10.1, 31744x2048 12.9 -> 12.4
+// against 13.8, 28672x4096 26.3 -> 22.5 against 23.3, 28672x8192 45.4 -> 41.0
+// against 49.0, 53248x4096 46.5 -> 40.4 against 45.9, 28672x11008 80.9 -> 59.9
+// against 67.1, 16384x16384 62.4 -> 48.6 against 54.5. Config 1 (eight slices)
+// holds two workgroups per CU; where that leaves a second, part-filled
+// generation, four slices (five per CU) are faster up to 8 KB: 12288x8192
+// 20.8 -> 18.0 against 20.2, 8720x8192 17.9 -> 14.0 against 19.1. With more
+// wavefronts config 0 stays (49152x2048 17.6 against 18.1), and above 8
+// columns, where it already was ahead, the lowest cost (53248x4096 N = 16 43.0
+// against 44.4).
 inline int gemm_narrow(int best, int64_t nrb, int nkb, int n_cu) {
     if (nkb > 128) return best == 0 || best == 3 ? 4 : best;
     if (best == 1 && nrb > 2 * (int64_t)n_cu) return 2;
-    return best == 0 && nkb >= 16 && (nrb <= 7 * (int64_t)n_cu || nkb % 64 == 0) ? 2 : best;
+    return best == 0 && nkb >= 16 && (nrb < 8 * (int64_t)n_cu || nkb % 64 == 0) ? 2 : best;
 }
 static_assert(kGemmCfgs[2].R == 1 && kGemmCfgs[2].WK == 4 && kGemmCfgs[3].R == 2 && kGemmCfgs[3].WK == 4 &&
                   kGemmCfgs[4].R == 2 && kGemmCfgs[4].WK == 8,

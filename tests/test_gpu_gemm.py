@@ -32,6 +32,10 @@ SHAPES = [
     (8208, 704, 200, (2, 4, 2, 2, 1)),      # several chunks
     (12304, 704, 500, (4, 4, 2, 2, 1)),     # several chunks
     (48, 130048, 3, (1, 1, 1, 1, 8)),       # the longest k
+    # large matrices at up to 8 columns
+    (28688, 1600, 1, (1, 1, 1, 1, 4)),
+    (8720, 8128, 5, (1, 1, 1, 1, 4)),
+    (16400, 8256, 3, (2, 1, 1, 1, 8)),
 ]
 
 

@@ -128,3 +128,21 @@ def test_most_rows(torch_cuda):
     for v in (y, yf):
         v = v.view(N, M // rep, rep)
         assert bool((v == v[:, :1]).all())
+
+
+@pytest.mark.parametrize("form", ["plain", "reordered", "w2"])
+@pytest.mark.parametrize("M,K,N", [
+    (7536, 2496, 16), (3312, 4800, 12),                 # one 11-LT chunk per wavefront
+    (10832, 1536, 4), (23184, 896, 3),                  # short slices, two row blocks
+    (41008, 128, 17), (49168, 192, 32), (49168, 256, 1),            # row blocks of few LTs
+    (81936, 704, 3), (49168, 384, 7), (131088, 384, 25),
+])
+def test_calls_the_chunked_kernel_keeps(torch_cuda, M, K, N, form):
+    """Both sides of the rules that keep narrow calls off the tile kernel."""
+    announce(f"route {form} M={M} K={K} N={N}")
+    if form == "plain" and torch_cuda.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert tile_config(M, K, N, form) is None
+    bits = 2 if form == "w2" else 4
+    W, Xt, sc = synth.random_problem(M, K, N, 0.5, M + K + N, bits=bits)
+    Y, Yf = run_spmm(torch_cuda, W, Xt, sc, reorder=form == "reordered", bits=bits)
+    check(Y, Yf, W, Xt, sc)

@@ -129,11 +129,12 @@ def test_gemm_tests_run_every_configuration():
 @pytest.mark.parametrize("M,K,N,row_blocks,split_k", [
     # Large matrices at few columns: slower than the kernel before this one without K slices, or with four long ones
     (28672, 4096, 1, 1, 4), (28672, 8192, 8, 1, 4), (53248, 4096, 1, 1, 4), (28672, 1536, 1, 1, 4),
+    (28688, 1024, 1, 1, 4), (32752, 2048, 8, 1, 4),
     (28672, 11008, 1, 2, 8), (16384, 16384, 1, 2, 8),
     # or with more than one generation of eight
     (12288, 8192, 1, 1, 4), (11280, 8192, 8, 1, 4),
     # and those that it keeps
-    (28672, 768, 1, 1, 1), (49152, 2048, 1, 1, 1), (12288, 256, 1, 1, 1), (28672, 2048, 16, 1, 1), (8192, 8192, 1, 2, 8),
+    (28672, 768, 1, 1, 1), (32768, 2048, 1, 1, 1), (49152, 2048, 1, 1, 1), (12288, 256, 1, 1, 1), (28672, 2048, 16, 1, 1), (8192, 8192, 1, 2, 8),
     (4096, 11008, 8, 1, 8),
 ])
 def test_gemm_choice_of_large_narrow_products(M, K, N, row_blocks, split_k):
