@@ -207,16 +207,20 @@ us_status make_plan(int M, int K, int N, bool perm, int bits, const us_spmm_opts
 // row block, or half of one, while the tile kernel's chunks of four LTs are
 // split over two wavefronts or more and mostly empty. us per call, chunked
 // against tile: 1048576x128 N = 1 33.5 / 64.1, N = 32 82.8 / 110.8; 262144x256
-// N = 1 12.5 / 19.3, N = 16 17.3 / 21.8, N = 32 23.9 / 30.5; 49152x256 N = 8 to
-// 32 22-30 % apart; at 32768 rows level. Longer row blocks: 81920x512 N = 1
-// 17 %, 262144x768 N = 1 22 %, 524288x320 N = 8 7 %, 131072x320 N = 32 10 %;
-// at 9 to 16 columns, with 2-bit weights or 16 LTs the tile kernel is ahead.
+// N = 1 12.5 / 19.3, N = 16 17.3 / 21.8, N = 32 23.9 / 30.5. Where the line
+// lies, in row blocks on the busiest CU: up to 256 k the chunked kernel is
+// 13-23 % ahead from 9 on at 32 columns (level at 8), 3-9 % at one column and
+// with 2-bit weights, 3-10 % from 10 on at 8 and 16 columns. Longer row blocks:
+// 45056x320 to 45056x768 (11) 3-23 % ahead up to 4 columns, 40960x512 (10) 7 %
+// behind; 262144x768 N = 1 22 % ahead, 49136x512 N = 8 13 %, 262144x512 N = 8
+// 7 % behind, 524288x320 N = 8 7 % and 131072x320 N = 32 10 % ahead. At 9 to 16
+// columns, with 2-bit weights or 16 LTs the tile kernel is ahead there.
 bool tall(int nrb, int nkb, int N, int bits, int n_cu) {
-    const int per_cu = nrb / n_cu;
-    if (per_cu < 10 || N > 32) return false;
-    if (nkb <= 4) return true;
+    const int per_cu = (nrb + n_cu - 1) / n_cu;
+    if (per_cu < 9 || N > 32) return false;
+    if (nkb <= 4) return per_cu >= 10 || N > 16 || N <= 4 || bits == 2;
     if (N > 16) return nkb <= 6 && per_cu >= 32;
-    return bits == 4 && per_cu >= 12 && (N <= 4 ? nkb <= 12 : N <= 8 && nkb <= 6);
+    return bits == 4 && per_cu >= 11 && (N <= 4 ? nkb <= 12 : N <= 8 && nkb <= (per_cu <= 16 ? 8 : 6));
 }
 
 // Whether an automatic call takes the tile kernel (us_spmm_tile.h), which

@@ -135,7 +135,7 @@ def test_most_rows(torch_cuda):
     (7536, 2496, 16), (3312, 4800, 12),                 # one 11-LT chunk per wavefront
     (10832, 1536, 4), (23184, 896, 3),                  # short slices, two row blocks
     (41008, 128, 17), (49168, 192, 32), (49168, 256, 1),            # row blocks of few LTs
-    (81936, 704, 3), (49168, 384, 7), (131088, 384, 25),
+    (81936, 704, 3), (49168, 384, 7), (131088, 384, 25), (34816, 128, 29), (45072, 768, 2),
 ])
 def test_calls_the_chunked_kernel_keeps(torch_cuda, M, K, N, form):
     """Both sides of the rules that keep narrow calls off the tile kernel."""

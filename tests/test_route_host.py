@@ -39,7 +39,15 @@ FORMS = [(4, False), (4, True), (2, False)]
     (49152, 256, 16, "us_spmm_kernel", 1),
     (262144, 768, 1, "us_spmm_kernel", 1),
     (131072, 320, 32, "us_spmm_kernel", 1),
+    (34816, 128, 32, "us_spmm_kernel", 1),
+    (38912, 256, 8, "us_spmm_kernel", 1),
+    (45056, 768, 4, "us_spmm_kernel", 1),
+    (49136, 512, 8, "us_spmm_kernel", 1),
     (28672, 256, 16, "us_spmm_tile_kernel", 1),
+    (32768, 128, 32, "us_spmm_tile_kernel", 1),
+    (34816, 256, 8, "us_spmm_tile_kernel", 1),
+    (40960, 512, 1, "us_spmm_tile_kernel", 1),
+    (262144, 512, 8, "us_spmm_tile_kernel", 1),
     (262144, 320, 16, "us_spmm_tile_kernel", 1),
     (262144, 768, 24, "us_spmm_tile_kernel", 1),
     (262144, 256, 100, "us_spmm_tile_kernel", 1),
